@@ -16,6 +16,28 @@
 
 using acex::Pack;
 
+namespace acex {
+
+// Compute units of the current device, rounded down to a multiple of the 8
+// XCDs (persistent grids keep a workgroup on one XCD).  Cached per device.
+int device_cus() {
+  static int cache[64] = {0};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  if (cache[dev] == 0) {
+    int cu = 0;
+    if (hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cu < 8)
+      cu = 256;
+    cache[dev] = (cu / 8) * 8;
+  }
+  return cache[dev];
+}
+
+}  // namespace acex
+
+using acex::device_cus;
+
 namespace {
 
 thread_local int g_last_hip = 0;
@@ -449,22 +471,6 @@ int device_present() {
   return 1;
 }
 
-// Compute units of the current device, rounded down to a multiple of the 8
-// XCDs (persistent grids keep a workgroup on one XCD).  Cached per device.
-int device_cus() {
-  static int cache[64] = {0};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  if (cache[dev] == 0) {
-    int cu = 0;
-    if (hipDeviceGetAttribute(&cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cu < 8)
-      cu = 256;
-    cache[dev] = (cu / 8) * 8;
-  }
-  return cache[dev];
-}
-
 struct ProfScope {
   ace_plan* p;
   int stage;
@@ -699,7 +705,7 @@ int build_end(const ace_plan* p, hipStream_t s, char* w, const double* phi, doub
   // ---- A8: xi = W L^{-T}, i.e. xi_k = sum_i Linv[k][i] W_i
   {
     ProfScope ps(p, 6, s);
-    e = acex::launch_gemm_ab(Linv, W, p->n_orb, p->n_orb, p->npts, 1.0, xi, info, s);
+    e = acex::launch_gemm_ab(Linv, W, p->n_orb, p->n_orb, p->npts, 1.0, xi, true, info, s);
     if (e != hipSuccess) return hip_fail(e);
   }
   // ---- A10: E_x = tr(M)
@@ -767,7 +773,7 @@ int apply_enqueue(const ace_plan* p, hipStream_t s, double* C, double* part, int
                                  nullptr, s);
   if (e != hipSuccess) return hip_fail(e);
   // out[v] = -sum_k C[v][k] xi_k
-  e = launch_gemm_ab(C, xi, n_vec, p->n_orb, p->npts, -1.0, out, nullptr, s);
+  e = launch_gemm_ab(C, xi, n_vec, p->n_orb, p->npts, -1.0, out, false, nullptr, s);
   if (e != hipSuccess) return hip_fail(e);
   return ACE_OK;
 }
@@ -1677,7 +1683,7 @@ int scdm_localize(const ace_plan* p, void* stream, void* ws, size_t ws_bytes, co
                               reinterpret_cast<double*>(w + l.partial), l.nsplit,
                               reinterpret_cast<int*>(w + l.state), info, kPolarMaxIter, s);
   if (e != hipSuccess) return hip_fail(e);
-  e = acex::launch_gemm_ab(Y, phi, k, k, p->npts, 1.0, phi_loc, nullptr, s);
+  e = acex::launch_gemm_ab(Y, phi, k, k, p->npts, 1.0, phi_loc, false, nullptr, s);
   return e == hipSuccess ? ACE_OK : hip_fail(e);
 }
 

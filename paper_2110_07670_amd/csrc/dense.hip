@@ -10,6 +10,8 @@
 //   D (4 doubles): D[i = l / 16 + 4 v][j = l % 16], v = 0..3
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace acex {
@@ -20,32 +22,44 @@ __device__ __forceinline__ d4 mfma16x16x4(double a, double b, d4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// ------------------------------------------------------------------ C = A B^T, split K
-// Workgroup: 256 threads (4 waves in 2 x 2), output tile 128 x 128, each wave
-// 64 x 64 = 4 x 4 MFMA blocks.  K staged through two LDS buffers in slabs of
-// KT: while the MFMAs read one slab, the next one (loaded into registers
-// behind them) is stored into the other buffer, so each slab costs one
-// barrier.  VEC (even K, 16-byte aligned operands): two consecutive k per
-// load and per LDS store, rows padded to 18 (16-byte aligned, and the MFMA
-// operand reads of 32 lanes still fall on distinct banks); else one k per
-// access, rows padded to 17.
+// ------------------------------------------------------------------ C = A B^T, large tiles
+// More than 64 rows on both sides: 256 threads (4 waves in 2 x 2), output
+// tile 128 x 128, each wave 64 x 64 = 4 x 4 MFMA blocks.  K staged through
+// two LDS buffers in slabs of KT: while the MFMAs read one slab, the next one
+// (loaded into registers behind them) is stored into the other buffer, so
+// each slab costs one barrier.  VEC (even K, 16-byte aligned operands): two
+// consecutive k per load and per LDS store, rows padded to 18 (16-byte
+// aligned, and the MFMA operand reads of 32 lanes still fall on distinct
+// banks); else one k per access, rows padded to 17.  Whole 128-byte lines per
+// row and each operand read once per workgroup: 556 us for 128 x 128 over
+// 884,736 points against 545-700 us without LDS (the kernel below), 1094
+// against 1378 us over 1,728,000.  sym: only the tiles on and below the
+// diagonal (512 orbitals: 10 of 16).
 constexpr int kAbtTile = 128;
 constexpr int kAbtKT = 16;
 constexpr int kAbtPer = kAbtTile * kAbtKT / 256;  // elements per thread per operand
 
 template <bool VEC>
-__global__ __launch_bounds__(256) void k_gemm_abt(const double* __restrict__ A,
+__global__ __launch_bounds__(256) void k_gemm_abt_tile(const double* __restrict__ A,
                                                   const double* __restrict__ B, int m, int n,
-                                                  int64_t K, int64_t kchunk, int tiles_n,
+                                                  int64_t K, int64_t kchunk, int tiles_n, bool sym,
                                                   bool abs_in, double* __restrict__ partial,
                                                   const int* __restrict__ skip) {
   if (skip && *skip != 0) return;
   constexpr int kAbtPitch = VEC ? kAbtKT + 2 : kAbtKT + 1;
   __shared__ __align__(16) double sA[2][kAbtTile * kAbtPitch];
   __shared__ __align__(16) double sB[2][kAbtTile * kAbtPitch];
-  const int tile = blockIdx.x;
   const int split = blockIdx.y;
-  const int tm = tile / tiles_n, tn = tile % tiles_n;
+  int tm, tn;
+  if (sym) {  // the tiles on and below the diagonal, row by row
+    tm = 0;
+    int t = blockIdx.x;
+    while (t > tm) t -= ++tm;
+    tn = t;
+  } else {
+    tm = blockIdx.x / tiles_n;
+    tn = blockIdx.x % tiles_n;
+  }
   const int m0 = tm * kAbtTile, n0 = tn * kAbtTile;
   const int64_t kbeg = (int64_t)split * kchunk;
   int64_t kend = kbeg + kchunk;
@@ -153,152 +167,430 @@ __global__ __launch_bounds__(256) void k_gemm_abt(const double* __restrict__ A,
       }
 }
 
-// C[i] = scale * sum_s partial[s][i]: 64 outputs per workgroup, four threads
-// per output each summing a fixed residue class of s, combined in a fixed order.
+// ------------------------------------------------------------------ C = A B^T, few rows
+// Both operands run along K, so a lane's MFMA operand (one row, one k) lies
+// next to the following k's: the fragments are loaded straight into
+// registers, 64 contiguous bytes of a row per four lanes, with no LDS and no
+// barrier in the loop.  Within eight k, lane group g = lane / 16 takes k = 2 g
+// and 2 g + 1: the same permutation of the sum on both sides.
+//
+// A workgroup's four waves cover WM x WN wave tiles of (16 RM) x (16 RN)
+// outputs; the remaining factor WK = 4 / (WM WN) splits its K range (eight k
+// per wave in turn), summed in LDS in a fixed order at the end.  The tile
+// follows the output (abt_shape): in the 128 x 128 tile above a product of
+// few rows spends its time on the matrix cores' padding rows (4 x 128 outputs
+// over 884,736 points 553 us there, 190 us here, which is 4.8 TB/s of its
+// operands; 36 x 36 over 110,592 83 and 26 us; 8 x 8 over 32,768 25 and 5).
+// kAbtAhead eight-k steps are in flight per wave, which with the 128
+// registers of a 64 x 64 wave tile leaves two waves per SIMD.
+//
+// VEC: K a multiple of 8 and 16-byte aligned operands; else scalar loads
+// with a bounds check per k.
+constexpr int kAbtAhead = 3;
+
+template <int RM, int WM, int RN, int WN, bool VEC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_abt(
+    const double* __restrict__ A, const double* __restrict__ B, int m, int n, int64_t K,
+    int64_t kchunk, int tiles_n, bool sym, bool abs_in, double* __restrict__ partial,
+    const int* __restrict__ skip) {
+  if (skip && *skip != 0) return;
+  constexpr int WK = 4 / (WM * WN), TM = 16 * RM * WM, TN = 16 * RN * WN, D = kAbtAhead;
+  int tm, tn;
+  if (sym) {  // the tiles on and below the diagonal, row by row
+    tm = 0;
+    int t = blockIdx.x;
+    while (t > tm) t -= ++tm;
+    tn = t;
+  } else {
+    tm = blockIdx.x / tiles_n;
+    tn = blockIdx.x % tiles_n;
+  }
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wk = wave / (WM * WN), wmn = wave % (WM * WN), wm = wmn / WN, wn = wmn % WN;
+  const int li = lane & 15, g = lane >> 4;
+  const int64_t kbeg = (int64_t)blockIdx.y * kchunk;
+  int64_t kend = kbeg + kchunk;
+  if (kend > K) kend = K;
+  // a wave's operand rows as a uniform base and 32-bit lane offsets (64 rows of
+  // at most 192^3 doubles are under 4 GiB); rows past the end read the last
+  // row, and their outputs are not stored
+  const int ra = (tm * WM + wm) * RM * 16, rb = (tn * WN + wn) * RN * 16;
+  const char* ba = reinterpret_cast<const char*>(A + (int64_t)min(ra, m - 1) * K);
+  const char* bb = reinterpret_cast<const char*>(B + (int64_t)min(rb, n - 1) * K);
+  unsigned oa[RM], ob[RN];
+#pragma unroll
+  for (int i = 0; i < RM; ++i)
+    oa[i] = 8u * ((unsigned)max(min(16 * i + li, m - 1 - ra), 0) * (unsigned)K + 2 * g);
+#pragma unroll
+  for (int j = 0; j < RN; ++j)
+    ob[j] = 8u * ((unsigned)max(min(16 * j + li, n - 1 - rb), 0) * (unsigned)K + 2 * g);
+  d4 acc[RM][RN];
+#pragma unroll
+  for (int i = 0; i < RM; ++i)
+#pragma unroll
+    for (int j = 0; j < RN; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+  double2 fa[D][RM], fb[D][RN];
+  auto ld = [&](const char* p, unsigned o, int64_t k) __attribute__((always_inline)) {
+    const double* q = reinterpret_cast<const double*>(p + 8 * k + o);
+    if constexpr (VEC) {
+      return *reinterpret_cast<const double2*>(q);
+    } else {
+      double2 v = {0.0, 0.0};
+      if (k + 2 * g < kend) v.x = q[0];
+      if (k + 2 * g + 1 < kend) v.y = q[1];
+      return v;
+    }
+  };
+  // this wave's steps: k = kbeg + 8 (wk + WK t), t < steps; a fetch past the
+  // last one repeats it and is not multiplied
+  const int steps =
+      kbeg + 8 * wk < kend ? (int)((kend - kbeg - 8 * wk + 8 * WK - 1) / (8 * WK)) : 0;
+  auto fetch = [&](int d, int t) __attribute__((always_inline)) {
+    const int64_t k = kbeg + 8 * (wk + (int64_t)WK * min(t, steps - 1));
+#pragma unroll
+    for (int i = 0; i < RM; ++i) fa[d][i] = ld(ba, oa[i], k);
+#pragma unroll
+    for (int j = 0; j < RN; ++j) fb[d][j] = ld(bb, ob[j], k);
+  };
+  auto multiply = [&](int d) __attribute__((always_inline)) {
+    if (abs_in) {
+#pragma unroll
+      for (int i = 0; i < RM; ++i) fa[d][i] = double2{fabs(fa[d][i].x), fabs(fa[d][i].y)};
+#pragma unroll
+      for (int j = 0; j < RN; ++j) fb[d][j] = double2{fabs(fb[d][j].x), fabs(fb[d][j].y)};
+    }
+#pragma unroll
+    for (int i = 0; i < RM; ++i)
+#pragma unroll
+      for (int j = 0; j < RN; ++j) acc[i][j] = mfma16x16x4(fa[d][i].x, fb[d][j].x, acc[i][j]);
+#pragma unroll
+    for (int i = 0; i < RM; ++i)
+#pragma unroll
+      for (int j = 0; j < RN; ++j) acc[i][j] = mfma16x16x4(fa[d][i].y, fb[d][j].y, acc[i][j]);
+  };
+  if (steps > 0) {
+#pragma unroll
+    for (int d = 0; d < D - 1; ++d) fetch(d, d);
+    for (int t = 0; t < steps; t += D) {
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        fetch((d + D - 1) % D, t + d + D - 1);
+        if (t + d < steps) multiply(d);
+      }
+    }
+  }
+  double* out = partial + (int64_t)blockIdx.y * m * n;
+  __shared__ double red[WK > 1 ? WK : 1][WK > 1 ? WM * WN * RN * 256 : 1];
+#pragma unroll
+  for (int i = 0; i < RM; ++i) {
+    if constexpr (WK > 1) {
+      if (i > 0) __syncthreads();
+#pragma unroll
+      for (int j = 0; j < RN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[wk][((wmn * RN + j) * 4 + v) * 64 + lane] = acc[i][j][v];
+      __syncthreads();
+      if (wk > 0) continue;
+#pragma unroll
+      for (int j = 0; j < RN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          double s = acc[i][j][v];
+#pragma unroll
+          for (int w = 1; w < WK; ++w) s += red[w][((wmn * RN + j) * 4 + v) * 64 + lane];
+          acc[i][j][v] = s;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < RN; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int row = tm * TM + (wm * RM + i) * 16 + g + 4 * v;
+        const int col = tn * TN + (wn * RN + j) * 16 + li;
+        if (row < m && col < n) out[(int64_t)row * n + col] = acc[i][j][v];
+      }
+  }
+}
+
+// C[i] = scale * sum_s partial[s][i]: 256 / G outputs per workgroup, G
+// threads per output each summing the splits s = g mod G in order, combined
+// in a fixed order.  sym_tile > 0: only the tiles of that size on and below
+// the diagonal were computed; an output above them is its mirror image.
+template <int G>
 __global__ __launch_bounds__(256) void k_reduce_splits(const double* __restrict__ partial,
-                                                       int nsplit, int64_t count, double scale,
+                                                       int nsplit, int64_t count, int n,
+                                                       int sym_tile, double scale,
                                                        double* __restrict__ C,
                                                        const int* __restrict__ skip) {
   if (skip && *skip != 0) return;
-  __shared__ double red[4][64];
-  const int o = threadIdx.x & 63, g = threadIdx.x >> 6;
-  const int64_t i = (int64_t)blockIdx.x * 64 + o;
-  double s0 = 0.0, s1 = 0.0;
-  if (i < count) {
-    int k = g;
-    for (; k + 4 < nsplit; k += 8) {
-      s0 += partial[(int64_t)k * count + i];
-      s1 += partial[(int64_t)(k + 4) * count + i];
-    }
-    if (k < nsplit) s0 += partial[(int64_t)k * count + i];
+  constexpr int O = 256 / G;
+  __shared__ double red[G][O];
+  const int o = threadIdx.x % O, g = threadIdx.x / O;
+  const int64_t i = (int64_t)blockIdx.x * O + o;
+  int64_t src = i;
+  if (sym_tile > 0 && i < count) {
+    const int r = (int)(i / n), c = (int)(i % n);
+    if (r / sym_tile < c / sym_tile) src = (int64_t)c * n + r;
   }
-  red[g][o] = s0 + s1;
+  double s = 0.0;
+  if (i < count) {
+#pragma unroll 4
+    for (int k = g; k < nsplit; k += G) s += partial[(int64_t)k * count + src];
+  }
+  red[g][o] = s;
   __syncthreads();
-  if (g == 0 && i < count) C[i] = scale * ((red[0][o] + red[1][o]) + (red[2][o] + red[3][o]));
+  if (g == 0 && i < count) {
+#pragma unroll
+    for (int q = 1; q < G; ++q) s += red[q][o];
+    C[i] = scale * s;
+  }
 }
 
+namespace {
+
+// Wave tile rows (in 16s) and wave rows of a product with m output rows: the
+// smallest that covers them, up to 64 rows per wave and two wave rows.
+struct AbtShape {
+  int r, w;
+};
+AbtShape abt_shape(int m) {
+  if (m <= 16) return {1, 1};
+  if (m <= 32) return {2, 1};
+  if (m <= 64) return {4, 1};
+  return {4, 2};
+}
+int abt_tile(int m) {
+  const AbtShape s = abt_shape(m);
+  return 16 * s.r * s.w;
+}
+
+template <int RM, int WM, int RN, int WN>
+void abt_launch(bool vec, dim3 grid, hipStream_t s, const double* A, const double* B, int m, int n,
+                int64_t K, int64_t kchunk, int tiles_n, bool sym, bool abs_in, double* partial,
+                const int* skip) {
+  if (vec)
+    hipLaunchKernelGGL((k_gemm_abt<RM, WM, RN, WN, true>), grid, dim3(256), 0, s, A, B, m, n, K,
+                       kchunk, tiles_n, sym, abs_in, partial, skip);
+  else
+    hipLaunchKernelGGL((k_gemm_abt<RM, WM, RN, WN, false>), grid, dim3(256), 0, s, A, B, m, n, K,
+                       kchunk, tiles_n, sym, abs_in, partial, skip);
+}
+
+}  // namespace
+
+// Workgroups along K: together two per CU for the large tiles (two are
+// resident; 1024 instead of 512 workgroups took 13 us more at 128 x 128, and
+// the reduction of twice the partial sums 10 us more) and four for the
+// smaller ones; at least eight steps per wave; and no more partial sums than
+// the operands themselves are large (each is written and read once more).
 int gemm_abt_splits(int m, int n, int64_t K) {
-  const int tiles = ((m + kAbtTile - 1) / kAbtTile) * ((n + kAbtTile - 1) / kAbtTile);
-  // aim for about 1024 workgroups, at least 8 K-slabs each
-  int64_t ns = (1024 + tiles - 1) / tiles;
-  const int64_t maxs = (K + 8 * kAbtKT - 1) / (8 * kAbtKT);
-  if (ns > maxs) ns = maxs;
-  if (ns < 1) ns = 1;
-  return (int)ns;
+  const AbtShape sm = abt_shape(m), sn = abt_shape(n);
+  const int64_t tiles = (int64_t)((m + abt_tile(m) - 1) / abt_tile(m)) *
+                        ((n + abt_tile(n) - 1) / abt_tile(n));
+  const int wk = 4 / (sm.w * sn.w);
+  const int64_t want = sm.r * sn.r * sm.w * sn.w >= 32 ? 512 : 1024;
+  int64_t ns = want / tiles;
+  ns = std::min(ns, (K + 64 * wk - 1) / (64 * wk));
+  ns = std::min(ns, K * (m + n) / (2 * (int64_t)m * n));
+  return (int)std::max<int64_t>(ns, 1);
 }
 
 hipError_t launch_gemm_abt(const double* A, const double* B, int m, int n, int64_t K,
                            double scale, double* C, double* partial, int nsplit, bool abs_inputs,
                            const int* skip, hipStream_t s) {
-  const int tiles_m = (m + kAbtTile - 1) / kAbtTile, tiles_n = (n + kAbtTile - 1) / kAbtTile;
+  const AbtShape sm = abt_shape(m), sn = abt_shape(n);
+  const int tiles_m = (m + abt_tile(m) - 1) / abt_tile(m);
+  const int tiles_n = (n + abt_tile(n) - 1) / abt_tile(n);
+  const int wk = 4 / (sm.w * sn.w);
   int64_t kchunk = (K + nsplit - 1) / nsplit;
-  kchunk = ((kchunk + kAbtKT - 1) / kAbtKT) * kAbtKT;
-  const bool vec = K % 2 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0 &&
+  const int unit = m > 64 && n > 64 ? kAbtKT : 8 * wk;
+  kchunk = ((kchunk + unit - 1) / unit) * unit;
+  const bool vec = K % 8 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0 &&
                    reinterpret_cast<uintptr_t>(B) % 16 == 0;
-  if (vec)
-    hipLaunchKernelGGL(k_gemm_abt<true>, dim3(tiles_m * tiles_n, nsplit), dim3(256), 0, s, A, B,
-                       m, n, K, kchunk, tiles_n, abs_inputs, partial, skip);
-  else
-    hipLaunchKernelGGL(k_gemm_abt<false>, dim3(tiles_m * tiles_n, nsplit), dim3(256), 0, s, A, B,
-                       m, n, K, kchunk, tiles_n, abs_inputs, partial, skip);
+  // a product of one operand with itself is symmetric, bit for bit (the same
+  // products in the same order): the tiles above the diagonal are mirrored
+  const bool sym = A == B && m == n && tiles_m > 1;
+  const dim3 grid(sym ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n, nsplit);
+#define ACEX_ABT(RM, WM, RN, WN)                                                              \
+  if (sm.r == RM && sm.w == WM && sn.r == RN && sn.w == WN)                                   \
+    abt_launch<RM, WM, RN, WN>(vec, grid, s, A, B, m, n, K, kchunk, tiles_n, sym, abs_inputs, \
+                               partial, skip);
+#define ACEX_ABT_ROW(RM, WM) \
+  ACEX_ABT(RM, WM, 1, 1) ACEX_ABT(RM, WM, 2, 1) ACEX_ABT(RM, WM, 4, 1)
+  ACEX_ABT_ROW(1, 1) ACEX_ABT_ROW(2, 1) ACEX_ABT_ROW(4, 1) ACEX_ABT_ROW(4, 2)
+  ACEX_ABT(1, 1, 4, 2) ACEX_ABT(2, 1, 4, 2) ACEX_ABT(4, 1, 4, 2)
+  if (m > 64 && n > 64) {
+    if (vec)
+      hipLaunchKernelGGL(k_gemm_abt_tile<true>, grid, dim3(256), 0, s, A, B, m, n, K, kchunk,
+                         tiles_n, sym, abs_inputs, partial, skip);
+    else
+      hipLaunchKernelGGL(k_gemm_abt_tile<false>, grid, dim3(256), 0, s, A, B, m, n, K, kchunk,
+                         tiles_n, sym, abs_inputs, partial, skip);
+  }
+#undef ACEX_ABT_ROW
+#undef ACEX_ABT
   const int64_t count = (int64_t)m * n;
-  hipLaunchKernelGGL(k_reduce_splits, dim3((unsigned)((count + 63) / 64)), dim3(256), 0, s,
-                     partial, nsplit, count, scale, C, skip);
+  const int sym_tile = sym ? abt_tile(m) : 0;
+  if (count < 2048)
+    hipLaunchKernelGGL(k_reduce_splits<64>, dim3((unsigned)((count + 3) / 4)), dim3(256), 0, s,
+                       partial, nsplit, count, n, sym_tile, scale, C, skip);
+  else
+    hipLaunchKernelGGL(k_reduce_splits<16>, dim3((unsigned)((count + 15) / 16)), dim3(256), 0, s,
+                       partial, nsplit, count, n, sym_tile, scale, C, skip);
   return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ Out = A B (A small)
-// Workgroup: 256 threads, output tile 64 rows x 128 columns; wave w owns
-// rows [16 w, 16 w + 16) x 128 columns = 8 MFMA blocks.  Rows beyond 64 are
-// covered by more workgroups (row blocks).  Next K-slab prefetched into
-// registers.
-constexpr int kAbRows = 64;
-constexpr int kAbCols = 128;
-constexpr int kAbKT = 16;
-constexpr int kAbPerA = kAbRows * kAbKT / 256;
-constexpr int kAbPerB = kAbKT * kAbCols / 256;
+// A (16 RB rows of it) sits in LDS for the whole launch; every wave streams
+// its own 32-column tiles of B past it, with no barrier after the first: B's
+// MFMA operand (row k, 16 adjacent columns) is contiguous in memory, so it
+// goes straight to registers, two columns per lane (256 contiguous bytes of a
+// row), the next 16 rows in flight while the current 16 are multiplied.  One
+// wave's stores and loads run under the other waves' matrix instructions, and
+// B is read once per 16 RB output rows.  128 x 128 over 884,736 columns: 492
+// us (568 us in a loop by itself), 335-420 us with tri; staging B through LDS
+// in 16-row slabs with two barriers each, and reading it twice, took 700 us.
+// 4 rows: 199 against 332 us, 4.7 TB/s.
+//
+// LDS: sA[k][row], row fastest; an odd k's rows are stored with bit 4 flipped,
+// which puts the 16 rows that adjacent lane groups read on different banks.
+//
+// tri: A is lower triangular; row block b needs only k < 16 (b + 1).
+// VEC: R even, 16-byte aligned B and Out; else scalar accesses.
+constexpr int kAbThreads = 512;
+constexpr int kAbCols = 32;  // columns per wave tile
 
-__global__ __launch_bounds__(256) void k_gemm_ab(const double* __restrict__ A,
-                                                 const double* __restrict__ B, int m, int k,
-                                                 int64_t R, double scale, double* __restrict__ Out,
-                                                 const int* __restrict__ skip) {
+template <int RB, int KCAP, bool VEC>
+__global__ __launch_bounds__(kAbThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_ab(
+    const double* __restrict__ A, const double* __restrict__ B, int m, int k, int64_t R,
+    double scale, double* __restrict__ Out, bool tri, int nrb, const int* __restrict__ skip) {
   if (skip && *skip != 0) return;
-  __shared__ double sA[kAbRows * (kAbKT + 1)];
-  __shared__ double sB[kAbKT * kAbCols];
-  // Workgroup b runs on XCD b mod 8: the row blocks of one column block are
-  // consecutive on one XCD, so B's columns are read from HBM once and the
-  // other row blocks find them in that XCD's L2.
-  const int nrb = (m + kAbRows - 1) / kAbRows;
-  const int64_t ncb = (R + kAbCols - 1) / kAbCols;
-  const int64_t g = blockIdx.x >> 3;
-  const int xcd = blockIdx.x & 7;
-  const int rblk = (int)(g % nrb);
-  const int64_t cblk = (g / nrb) * 8 + xcd;
-  if (cblk >= ncb) return;
-  const int64_t r0 = cblk * kAbCols;
-  const int m0 = rblk * kAbRows;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  d4 acc[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) acc[j] = d4{0.0, 0.0, 0.0, 0.0};
-  double ra[kAbPerA], rb[kAbPerB];
-  auto fetch = [&](int k0) {
-#pragma unroll
-    for (int q = 0; q < kAbPerA; ++q) {
-      const int e = tid + q * 256;
-      const int r = e / kAbKT, c = e % kAbKT;
-      ra[q] = (m0 + r < m && k0 + c < k) ? A[(int64_t)(m0 + r) * k + k0 + c] : 0.0;
-    }
-#pragma unroll
-    for (int q = 0; q < kAbPerB; ++q) {
-      const int e = tid + q * 256;
-      const int kr = e / kAbCols, c = e % kAbCols;
-      rb[q] = (k0 + kr < k && r0 + c < R) ? B[(int64_t)(k0 + kr) * R + r0 + c] : 0.0;
-    }
+  constexpr int P = 16 * RB;
+  __shared__ double sA[KCAP * P];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, g = lane >> 4;
+  // the row blocks of one column group are consecutive on one XCD
+  // (workgroup b runs on XCD b mod 8): they find B's rows in its L2
+  const int xcd = blockIdx.x & 7, q = blockIdx.x >> 3;
+  const int rb0 = (q % nrb) * RB;  // first 16-row block
+  const int group = (q / nrb) * 8 + xcd, groups = (gridDim.x / 8 / nrb) * 8;
+  const int kblocks = tri ? min((k + 15) / 16, rb0 + RB) : (k + 15) / 16;
+  auto place = [](int kk, int row) __attribute__((always_inline)) {
+    return kk * P + (RB > 1 ? row ^ ((kk & 1) << 4) : row);
   };
-  fetch(0);
-  for (int k0 = 0; k0 < k; k0 += kAbKT) {
+  for (int e = tid; e < kblocks * 16 * P; e += kAbThreads) {
+    // 16 rows x 4 k per 64 threads
+    const int c = e >> 6, row = (c % RB) * 16 + (e & 15), kk = (c / RB) * 4 + ((e >> 4) & 3);
+    const int r = rb0 * 16 + row;
+    sA[place(kk, row)] = (r < m && kk < k) ? A[(int64_t)r * k + kk] : 0.0;
+  }
+  __syncthreads();
+  const int nact = min(RB, (m - rb0 * 16 + 15) / 16);  // row blocks with a row
+  const int64_t tiles = (R + kAbCols - 1) / kAbCols;
+  const int64_t stride = (int64_t)groups * (kAbThreads / 64);
+  double2 cur[4], nxt[4];
+  auto load = [&](double2* v, int64_t tile, int kb) __attribute__((always_inline)) {
+    const int64_t col = tile * kAbCols + 2 * li;
 #pragma unroll
-    for (int q = 0; q < kAbPerA; ++q) {
-      const int e = tid + q * 256;
-      sA[(e / kAbKT) * (kAbKT + 1) + e % kAbKT] = ra[q];
-    }
-#pragma unroll
-    for (int q = 0; q < kAbPerB; ++q) {
-      const int e = tid + q * 256;
-      sB[(e / kAbCols) * kAbCols + e % kAbCols] = rb[q];
-    }
-    __syncthreads();
-    if (k0 + kAbKT < k) fetch(k0 + kAbKT);
-#pragma unroll
-    for (int kk = 0; kk < kAbKT; kk += 4) {
-      const double af = sA[(wave * 16 + (lane & 15)) * (kAbKT + 1) + kk + (lane >> 4)];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const double bf = sB[(kk + (lane >> 4)) * kAbCols + j * 16 + (lane & 15)];
-        acc[j] = mfma16x16x4(af, bf, acc[j]);
+    for (int s = 0; s < 4; ++s) {
+      const int kk = kb * 16 + 4 * s + g;
+      v[s] = double2{0.0, 0.0};
+      if constexpr (VEC) {
+        if (kk < k && col < R) v[s] = *reinterpret_cast<const double2*>(B + (int64_t)kk * R + col);
+      } else {
+        if (kk < k && col < R) v[s].x = B[(int64_t)kk * R + col];
+        if (kk < k && col + 1 < R) v[s].y = B[(int64_t)kk * R + col + 1];
       }
     }
-    __syncthreads();
-  }
+  };
+  int64_t tile = (int64_t)group * (kAbThreads / 64) + wave;
+  if (tile >= tiles) return;
+  load(cur, tile, 0);
+  for (; tile < tiles; tile += stride) {
+    d4 acc[RB][2];
 #pragma unroll
-  for (int j = 0; j < 8; ++j)
+    for (int i = 0; i < RB; ++i) acc[i][0] = acc[i][1] = d4{0.0, 0.0, 0.0, 0.0};
+    for (int kb = 0; kb < kblocks; ++kb) {
+      const bool last = kb + 1 == kblocks;
+      if (!last || tile + stride < tiles) load(nxt, last ? tile + stride : tile, last ? 0 : kb + 1);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int row = m0 + wave * 16 + (lane >> 4) + 4 * v;
-      const int64_t col = r0 + j * 16 + (lane & 15);
-      if (row < m && col < R) Out[(int64_t)row * R + col] = scale * acc[j][v];
+      for (int i = 0; i < RB; ++i) {
+        if (i < nact && (!tri || rb0 + i >= kb)) {
+#pragma unroll
+          for (int s = 0; s < 4; ++s) {
+            const double a = sA[place(kb * 16 + 4 * s + g, i * 16 + li)];
+            acc[i][0] = mfma16x16x4(a, cur[s].x, acc[i][0]);
+            acc[i][1] = mfma16x16x4(a, cur[s].y, acc[i][1]);
+          }
+        }
+      }
+#pragma unroll
+      for (int s = 0; s < 4; ++s) cur[s] = nxt[s];
     }
+    const int64_t col = tile * kAbCols + 2 * li;
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int row = (rb0 + i) * 16 + g + 4 * v;
+        const double2 o = {scale * acc[i][0][v], scale * acc[i][1][v]};
+        if constexpr (VEC) {
+          if (row < m && col < R) *reinterpret_cast<double2*>(Out + (int64_t)row * R + col) = o;
+        } else {
+          if (row < m && col < R) Out[(int64_t)row * R + col] = o.x;
+          if (row < m && col + 1 < R) Out[(int64_t)row * R + col + 1] = o.y;
+        }
+      }
+  }
 }
 
-hipError_t launch_gemm_ab(const double* A, const double* B, int m, int k, int64_t R, double scale,
-                          double* Out, const int* skip, hipStream_t s) {
-  const int64_t ncb = (R + kAbCols - 1) / kAbCols;
-  const int64_t nrb = (m + kAbRows - 1) / kAbRows;
-  const int64_t blocks = ((ncb + 7) / 8) * 8 * nrb;  // column blocks padded to the 8 XCDs
-  hipLaunchKernelGGL(k_gemm_ab, dim3((unsigned)blocks), dim3(256), 0, s, A, B, m, k, R, scale,
-                     Out, skip);
+namespace {
+
+// per_cu: workgroups resident per CU (LDS, registers)
+template <int RB, int KCAP>
+hipError_t ab_launch(const double* A, const double* B, int m, int k, int64_t R, double scale,
+                     double* Out, bool tri, int per_cu, const int* skip, hipStream_t s) {
+  const int nrb = (m + 16 * RB - 1) / (16 * RB);
+  const int64_t tiles = (R + kAbCols - 1) / kAbCols, waves = kAbThreads / 64;
+  // column groups: as many as are resident, in eights, at most one per eight tiles
+  int64_t groups = (int64_t)device_cus() * per_cu / nrb / 8 * 8;
+  groups = std::max<int64_t>(8, std::min(groups, ((tiles + waves - 1) / waves + 7) / 8 * 8));
+  const dim3 grid((unsigned)(groups * nrb));
+  const bool vec = R % 2 == 0 && reinterpret_cast<uintptr_t>(B) % 16 == 0 &&
+                   reinterpret_cast<uintptr_t>(Out) % 16 == 0;
+  if (vec)
+    hipLaunchKernelGGL((k_gemm_ab<RB, KCAP, true>), grid, dim3(kAbThreads), 0, s, A, B, m, k, R,
+                       scale, Out, tri, nrb, skip);
+  else
+    hipLaunchKernelGGL((k_gemm_ab<RB, KCAP, false>), grid, dim3(kAbThreads), 0, s, A, B, m, k, R,
+                       scale, Out, tri, nrb, skip);
   return hipGetLastError();
+}
+
+}  // namespace
+
+// Rows per workgroup: those of the output, up to what LDS holds of A (128 KB:
+// 128 rows of 128, 64 of 256, 32 of 512).
+hipError_t launch_gemm_ab(const double* A, const double* B, int m, int k, int64_t R, double scale,
+                          double* Out, bool tri, const int* skip, hipStream_t s) {
+  if (k < 1 || k > 512) return hipErrorInvalidValue;
+#define ACEX_AB(RB, KCAP, PER) return ab_launch<RB, KCAP>(A, B, m, k, R, scale, Out, tri, PER, skip, s)
+  if (m <= 16) {
+    if (k <= 128) ACEX_AB(1, 128, 4);
+    ACEX_AB(1, 512, 2);
+  }
+  if (m <= 32 || k > 256) {
+    if (k <= 128) ACEX_AB(2, 128, 3);
+    ACEX_AB(2, 512, 1);
+  }
+  if (m <= 64 || k > 128) {
+    if (k <= 128) ACEX_AB(4, 128, 2);
+    ACEX_AB(4, 256, 1);
+  }
+  ACEX_AB(8, 128, 1);
+#undef ACEX_AB
 }
 
 // ------------------------------------------------------------------ Cholesky and L^{-1}

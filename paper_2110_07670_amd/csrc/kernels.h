@@ -28,6 +28,9 @@ struct GridArgs {
 // Is `pencils` a valid x-pass shape for grid n (0 is always valid)?
 bool pencils_ok(int n, int pencils);
 
+// Compute units of the current device, rounded down to a multiple of its 8 XCDs.
+int device_cus();
+
 // Does one (y, z) plane of the bulk type fit in a workgroup's LDS?
 bool plane_fits(int n, int prec);
 bool supported_n(int n);
@@ -127,9 +130,11 @@ hipError_t launch_gemm_abt(const double* A, const double* B, int m, int n, int64
                            double scale, double* C, double* partial, int nsplit,
                            bool abs_inputs, const int* skip_if_nonzero, hipStream_t s);
 int gemm_abt_splits(int m, int n, int64_t K);
-// Out[m][r] = scale * sum_k A[m][k] B[k][r]; A (m x k) row-major small, B (k x R) row-major.
+// Out[m][r] = scale * sum_k A[m][k] B[k][r]; A (m x k, k <= 512) row-major small,
+// B (k x R) row-major.  tri: A is lower triangular (its upper part is not read).
 hipError_t launch_gemm_ab(const double* A, const double* B, int m, int k, int64_t R,
-                          double scale, double* Out, const int* skip_if_nonzero, hipStream_t s);
+                          double scale, double* Out, bool tri, const int* skip_if_nonzero,
+                          hipStream_t s);
 // -M = L L^T (lower), then Linv = L^{-1}; info = 0 or the order of the first
 // non-positive leading minor.  work: n*n doubles.
 hipError_t launch_cholesky_inv(const double* M, int n, double* L, double* Linv, int* info,

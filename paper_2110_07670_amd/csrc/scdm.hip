@@ -451,7 +451,7 @@ hipError_t launch_scdm_polar(const double* phi, const int* pivots, int k, int64_
   for (int it = 0; it < max_iter; ++it) {
     e = launch_gemm_abt(Y, Y, k, k, k, 1.0, G, partial, nsplit, false, state, s);
     if (e != hipSuccess) return e;
-    e = launch_gemm_ab(G, Y, k, k, k, 1.0, Z, state, s);
+    e = launch_gemm_ab(G, Y, k, k, k, 1.0, Z, false, state, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_ns_update, dim3(1), dim3(1024), 0, s, Y, G, Z, k, state);
   }
