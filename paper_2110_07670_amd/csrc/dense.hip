@@ -11,6 +11,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 
 #include "kernels.h"
 
@@ -446,12 +447,12 @@ hipError_t launch_gemm_abt(const double* A, const double* B, int m, int n, int64
 // its own 32-column tiles of B past it, with no barrier after the first: B's
 // MFMA operand (row k, 16 adjacent columns) is contiguous in memory, so it
 // goes straight to registers, two columns per lane (256 contiguous bytes of a
-// row), the next 16 rows in flight while the current 16 are multiplied.  One
-// wave's stores and loads run under the other waves' matrix instructions, and
-// B is read once per 16 RB output rows.  128 x 128 over 884,736 columns: 492
-// us (568 us in a loop by itself), 335-420 us with tri; staging B through LDS
-// in 16-row slabs with two barriers each, and reading it twice, took 700 us.
-// 4 rows: 199 against 332 us, 4.7 TB/s.
+// row), 32 rows ahead of the multiplication (16 ahead, the loads issued after
+// a tile's stores waited for these: 708 against 588 us).  One wave's stores
+// and loads run under the other waves' matrix instructions, and B is read once
+// per 16 RB output rows.  128 x 128 over 884,736 columns: 588 us, 397 us with
+// tri; staging B through LDS in 16-row slabs with two barriers each, and
+// reading it twice, took 700 us.  4 rows: 199 against 332 us, 4.7 TB/s.
 //
 // LDS: sA[k][row], row fastest; an odd k's rows are stored with bit 4 flipped,
 // which puts the 16 rows that adjacent lane groups read on different banks.
@@ -490,7 +491,7 @@ __global__ __launch_bounds__(kAbThreads) __attribute__((amdgpu_waves_per_eu(2)))
   const int nact = min(RB, (m - rb0 * 16 + 15) / 16);  // row blocks with a row
   const int64_t tiles = (R + kAbCols - 1) / kAbCols;
   const int64_t stride = (int64_t)groups * (kAbThreads / 64);
-  double2 cur[4], nxt[4];
+  double2 cur[4], nxt[4], far[4];
   auto load = [&](double2* v, int64_t tile, int kb) __attribute__((always_inline)) {
     const int64_t col = tile * kAbCols + 2 * li;
 #pragma unroll
@@ -507,14 +508,21 @@ __global__ __launch_bounds__(kAbThreads) __attribute__((amdgpu_waves_per_eu(2)))
   };
   int64_t tile = (int64_t)group * (kAbThreads / 64) + wave;
   if (tile >= tiles) return;
+  // 16-row block kb + ahead of the wave's stream of blocks, past a tile's end
+  // the next tile's
+  auto load_ahead = [&](double2* v, int kb, int ahead) __attribute__((always_inline)) {
+    int64_t t = tile;
+    for (kb += ahead; kb >= kblocks; kb -= kblocks) t += stride;
+    if (t < tiles) load(v, t, kb);
+  };
   load(cur, tile, 0);
+  load_ahead(nxt, 0, 1);
   for (; tile < tiles; tile += stride) {
     d4 acc[RB][2];
 #pragma unroll
     for (int i = 0; i < RB; ++i) acc[i][0] = acc[i][1] = d4{0.0, 0.0, 0.0, 0.0};
     for (int kb = 0; kb < kblocks; ++kb) {
-      const bool last = kb + 1 == kblocks;
-      if (!last || tile + stride < tiles) load(nxt, last ? tile + stride : tile, last ? 0 : kb + 1);
+      load_ahead(far, kb, 2);
 #pragma unroll
       for (int i = 0; i < RB; ++i) {
         if (i < nact && (!tri || rb0 + i >= kb)) {
@@ -527,7 +535,10 @@ __global__ __launch_bounds__(kAbThreads) __attribute__((amdgpu_waves_per_eu(2)))
         }
       }
 #pragma unroll
-      for (int s = 0; s < 4; ++s) cur[s] = nxt[s];
+      for (int s = 0; s < 4; ++s) {
+        cur[s] = nxt[s];
+        nxt[s] = far[s];
+      }
     }
     const int64_t col = tile * kAbCols + 2 * li;
 #pragma unroll
@@ -548,14 +559,27 @@ __global__ __launch_bounds__(kAbThreads) __attribute__((amdgpu_waves_per_eu(2)))
 
 namespace {
 
-// per_cu: workgroups resident per CU (LDS, registers)
+// workgroups resident per CU (LDS, registers), looked up once per kernel
+template <int RB, int KCAP>
+int ab_per_cu() {
+  static std::atomic<int> cached{0};
+  int occ = cached.load(std::memory_order_relaxed);
+  if (occ > 0) return occ;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_gemm_ab<RB, KCAP, true>, kAbThreads,
+                                                   0) != hipSuccess ||
+      occ < 1)
+    occ = 1;
+  cached.store(occ, std::memory_order_relaxed);
+  return occ;
+}
+
 template <int RB, int KCAP>
 hipError_t ab_launch(const double* A, const double* B, int m, int k, int64_t R, double scale,
-                     double* Out, bool tri, int per_cu, const int* skip, hipStream_t s) {
+                     double* Out, bool tri, const int* skip, hipStream_t s) {
   const int nrb = (m + 16 * RB - 1) / (16 * RB);
   const int64_t tiles = (R + kAbCols - 1) / kAbCols, waves = kAbThreads / 64;
   // column groups: as many as are resident, in eights, at most one per eight tiles
-  int64_t groups = (int64_t)device_cus() * per_cu / nrb / 8 * 8;
+  int64_t groups = (int64_t)device_cus() * ab_per_cu<RB, KCAP>() / nrb / 8 * 8;
   groups = std::max<int64_t>(8, std::min(groups, ((tiles + waves - 1) / waves + 7) / 8 * 8));
   const dim3 grid((unsigned)(groups * nrb));
   const bool vec = R % 2 == 0 && reinterpret_cast<uintptr_t>(B) % 16 == 0 &&
@@ -576,20 +600,20 @@ hipError_t ab_launch(const double* A, const double* B, int m, int k, int64_t R, 
 hipError_t launch_gemm_ab(const double* A, const double* B, int m, int k, int64_t R, double scale,
                           double* Out, bool tri, const int* skip, hipStream_t s) {
   if (k < 1 || k > 512) return hipErrorInvalidValue;
-#define ACEX_AB(RB, KCAP, PER) return ab_launch<RB, KCAP>(A, B, m, k, R, scale, Out, tri, PER, skip, s)
+#define ACEX_AB(RB, KCAP) return ab_launch<RB, KCAP>(A, B, m, k, R, scale, Out, tri, skip, s)
   if (m <= 16) {
-    if (k <= 128) ACEX_AB(1, 128, 4);
-    ACEX_AB(1, 512, 2);
+    if (k <= 128) ACEX_AB(1, 128);
+    ACEX_AB(1, 512);
   }
   if (m <= 32 || k > 256) {
-    if (k <= 128) ACEX_AB(2, 128, 3);
-    ACEX_AB(2, 512, 1);
+    if (k <= 128) ACEX_AB(2, 128);
+    ACEX_AB(2, 512);
   }
   if (m <= 64 || k > 128) {
-    if (k <= 128) ACEX_AB(4, 128, 2);
-    ACEX_AB(4, 256, 1);
+    if (k <= 128) ACEX_AB(4, 128);
+    ACEX_AB(4, 256);
   }
-  ACEX_AB(8, 128, 1);
+  ACEX_AB(8, 128);
 #undef ACEX_AB
 }
 
