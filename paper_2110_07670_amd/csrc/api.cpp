@@ -1580,9 +1580,10 @@ namespace {
 
 struct ScdmLayout {
   size_t rho, g, part, means, cnt, off, pre_total;
-  size_t A, nrm, perm, v, tau, rdiag, Y, G, Z, partial, state, loc_total;
-  int nsplit;
+  size_t A, pos, perm, cand, Y, G, Z, sq, err, state, loc_total;
 };
+
+constexpr int kPolarMaxIter = 100;
 
 ScdmLayout scdm_layout(const ace_plan* p, int m) {
   ScdmLayout l{};
@@ -1602,35 +1603,30 @@ ScdmLayout scdm_layout(const ace_plan* p, int m) {
   o += align256((size_t)nb * 4);
   l.pre_total = o;
   const int k = p->n_orb;
-  l.nsplit = acex::gemm_abt_splits(k, k, k);
   o = 0;
   l.A = o;
-  o += align256((size_t)std::max(m, 1) * k * 8);
-  l.nrm = o;
-  o += align256((size_t)std::max(m, 1) * 8);
+  o += align256((size_t)std::max(m, 1) * acex::scdm_qr_pitch(k) * 8);
+  l.pos = o;
+  o += align256((size_t)std::max(m, 1) * 4);
   l.perm = o;
   o += align256((size_t)std::max(m, 1) * 4);
-  l.v = o;
-  o += align256((size_t)k * 8);
-  l.tau = o;
-  o += align256(8);
-  l.rdiag = o;
-  o += align256((size_t)k * 8);
+  l.cand = o;
+  o += align256((size_t)2 * acex::scdm_qr_groups(m) * acex::kScdmCandBytes);
   l.Y = o;
   o += align256((size_t)k * k * 8);
   l.G = o;
   o += align256((size_t)k * k * 8);
   l.Z = o;
   o += align256((size_t)k * k * 8);
-  l.partial = o;
-  o += align256((size_t)l.nsplit * k * k * 8);
+  l.sq = o;
+  o += align256((size_t)k * 8);
+  l.err = o;
+  o += align256((size_t)kPolarMaxIter * 8);
   l.state = o;
   o += align256(16);
   l.loc_total = o;
   return l;
 }
-
-constexpr int kPolarMaxIter = 100;
 
 }  // namespace
 
@@ -1673,14 +1669,14 @@ int scdm_localize(const ace_plan* p, void* stream, void* ws, size_t ws_bytes, co
   hipError_t e = acex::launch_set_int(info, 0, s);
   if (e != hipSuccess) return hip_fail(e);
   e = acex::launch_scdm_qr(phi, points, m, k, p->npts, reinterpret_cast<double*>(w + l.A),
-                           reinterpret_cast<double*>(w + l.nrm), reinterpret_cast<int*>(w + l.perm),
-                           reinterpret_cast<double*>(w + l.v), reinterpret_cast<double*>(w + l.tau),
-                           reinterpret_cast<double*>(w + l.rdiag), pivots, info, s);
+                           reinterpret_cast<int*>(w + l.pos), reinterpret_cast<int*>(w + l.perm),
+                           w + l.cand, pivots, info, s);
   if (e != hipSuccess) return hip_fail(e);
   double* Y = reinterpret_cast<double*>(w + l.Y);
   e = acex::launch_scdm_polar(phi, pivots, k, p->npts, Y, reinterpret_cast<double*>(w + l.G),
                               reinterpret_cast<double*>(w + l.Z),
-                              reinterpret_cast<double*>(w + l.partial), l.nsplit,
+                              reinterpret_cast<double*>(w + l.sq),
+                              reinterpret_cast<double*>(w + l.err),
                               reinterpret_cast<int*>(w + l.state), info, kPolarMaxIter, s);
   if (e != hipSuccess) return hip_fail(e);
   e = acex::launch_gemm_ab(Y, phi, k, k, p->npts, 1.0, phi_loc, false, nullptr, s);

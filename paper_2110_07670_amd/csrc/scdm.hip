@@ -7,14 +7,14 @@
 //                  fixed-order means, and an ordered compaction of the kept
 //                  points (count per block, one scan, in-block prefix);
 //   pivoted QR   : Businger-Golub column pivoting on the n_orb x m matrix,
-//                  stored point-major (each column contiguous); per step one
-//                  workgroup picks the pivot (largest residual norm, first
-//                  index on a tie), swaps, and forms the Householder vector,
-//                  then one wave per remaining column applies it and
-//                  recomputes that column's residual norm;
+//                  stored point-major (each column contiguous); one launch
+//                  per step (k_qr_step);
 //   orthonormalisation : Newton-Schulz iteration Y <- (3 Y - Y Y^T Y) / 2
 //                  from Y = A_C^T / ||A_C||_F, which converges to the
-//                  orthogonal polar factor; the MFMA products of dense.hip.
+//                  orthogonal polar factor; two small MFMA launches per
+//                  iteration (k_ns_gram, k_ns_step).
+#include <algorithm>
+
 #include "kernels.h"
 
 namespace acex {
@@ -38,9 +38,29 @@ __device__ __forceinline__ double block_sum_1024(double v, double* red) {
   return s;
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+// v of the lane that the DPP control names (within rows of 16 lanes)
+template <int CTRL>
+__device__ __forceinline__ double dpp_move(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+// Sum over groups of G adjacent lanes, fixed order, the same value in every
+// lane of a group: a butterfly (xor 1, xor 2, then the mirrors, which pair
+// the quads and the halves of a row as xor 4 and xor 8 do).  Register moves up
+// to a row of 16 lanes: a shuffle per step would go through LDS.
+template <int G>
+__device__ __forceinline__ double group_sum(double v) {
+  v += dpp_move<0xB1>(v);                         // quad_perm 1 0 3 2
+  v += dpp_move<0x4E>(v);                         // quad_perm 2 3 0 1
+  v += dpp_move<0x141>(v);                        // row_half_mirror
+  if constexpr (G >= 16) v += dpp_move<0x140>(v);  // row_mirror
+  if constexpr (G >= 32) v += __shfl_xor(v, 16, 64);
+  if constexpr (G >= 64) v += __shfl_xor(v, 32, 64);
   return v;
 }
 
@@ -137,16 +157,30 @@ __global__ __launch_bounds__(256) void k_sel_count(const double* __restrict__ rh
   if (threadIdx.x == 0) cnt[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
-// exclusive scan of the block counts (one thread; a few thousand blocks)
-__global__ void k_sel_scan(const int* __restrict__ cnt, int nblk, int* __restrict__ off,
-                           int* __restrict__ total) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int s = 0;
-  for (int i = 0; i < nblk; ++i) {
+// exclusive scan of the block counts: each of 1024 threads scans a run of
+// blocks (a few thousand in all), the run totals are scanned in LDS
+__global__ __launch_bounds__(1024) void k_sel_scan(const int* __restrict__ cnt, int nblk,
+                                                   int* __restrict__ off,
+                                                   int* __restrict__ total) {
+  __shared__ int sums[1024];
+  const int t = threadIdx.x;
+  const int per = (nblk + 1023) / 1024, b0 = t * per, b1 = min(b0 + per, nblk);
+  int own = 0;
+  for (int i = b0; i < b1; ++i) own += cnt[i];
+  sums[t] = own;
+  __syncthreads();
+  for (int d = 1; d < 1024; d *= 2) {
+    const int v = t >= d ? sums[t - d] : 0;
+    __syncthreads();
+    sums[t] += v;
+    __syncthreads();
+  }
+  int s = sums[t] - own;
+  for (int i = b0; i < b1; ++i) {
     off[i] = s;
     s += cnt[i];
   }
-  *total = s;
+  if (t == 1023) *total = sums[1023];
 }
 
 // write the kept points of each block, in increasing order
@@ -175,224 +209,445 @@ __global__ __launch_bounds__(256) void k_sel_write(const double* __restrict__ rh
   }
 }
 
-// A (point-major, column j = point points[j], k values), residual norms, order
-__global__ __launch_bounds__(256) void k_qr_gather(const double* __restrict__ phi,
-                                                   const int* __restrict__ points, int m, int k,
-                                                   int64_t npts, double* __restrict__ A,
-                                                   double* __restrict__ nrm,
-                                                   int* __restrict__ perm) {
-  const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (j >= m) return;
-  const int64_t pt = points ? (int64_t)points[j] : (int64_t)j;
-  double s = 0.0;
-  for (int i = lane; i < k; i += 64) {
-    const double v = phi[(int64_t)i * npts + pt];
-    A[(int64_t)j * k + i] = v;
-    s += v * v;
-  }
-  s = wave_sum(s);
-  if (lane == 0) {
-    nrm[j] = s;
-    perm[j] = j;
-  }
+// ---- Pivoted QR, one launch per step.
+//
+// Columns stay where they are; pos[j] is the place of column j in the pivoted
+// order (the step that chose it, below s) and perm the column at each place
+// still open, so that ties resolve as if the columns were swapped.  Every
+// workgroup of a step finds the pivot by itself from the largest residual
+// norm that each workgroup of the step before left in cand (a few KB), reads
+// that one column (nobody writes it any more), forms the Householder vector in
+// registers, and applies it to its own columns, one wave per column, while it
+// looks for the largest residual norm of the next step.  A step takes 12 us at
+// the 18,000 columns of 128 that the preselection leaves on the 96^3 grid, the
+// same for the first and the last: it is the chain launch, candidates, pivot
+// column, sums that bounds it, not the 9 MB it moves on average.  A pivot
+// launch by one workgroup over all norms and an apply launch took 11.2 + 9.5.
+
+// A column that may be the next pivot: squared residual norm, place, index.
+struct __align__(16) QrCand {
+  double norm;
+  int pos, col;
+};
+static_assert(sizeof(QrCand) == kScdmCandBytes, "the workspace holds these");
+
+__device__ __forceinline__ bool cand_less(const QrCand& a, const QrCand& b) {
+  return b.norm > a.norm || (b.norm == a.norm && b.pos < a.pos);
 }
 
-// Step s: pivot (largest residual norm over columns s..m-1, first on a tie),
-// swap it into column s, Householder vector v (v[s] = 1, zeros above s) and
-// tau with (I - tau v v^T) A[s:, s] = beta e_s; info = s + 1 on a zero column.
-__global__ __launch_bounds__(1024) void k_qr_pivot(int s, int m, int k, double* __restrict__ A,
-                                                   double* __restrict__ nrm,
-                                                   int* __restrict__ perm, double* __restrict__ v,
-                                                   double* __restrict__ tau,
-                                                   double* __restrict__ rdiag,
-                                                   int* __restrict__ info) {
-  __shared__ double bv[16];
-  __shared__ int bi[16];
-  __shared__ double red[16];
-  __shared__ double sx0, sbeta;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  double best = -1.0;
-  int bidx = m;
-  for (int j = s + tid; j < m; j += 1024) {
-    const double x = nrm[j];
-    if (x > best) {  // strided scan visits increasing j: keeps the first maximum
-      best = x;
-      bidx = j;
+__device__ __forceinline__ double wave_max(double v) {
+  double o = dpp_move<0xB1>(v);
+  v = o > v ? o : v;
+  o = dpp_move<0x4E>(v);
+  v = o > v ? o : v;
+  o = dpp_move<0x141>(v);
+  v = o > v ? o : v;
+  o = dpp_move<0x140>(v);
+  v = o > v ? o : v;
+  const double a = lane_value(v, 0), b = lane_value(v, 16), c = lane_value(v, 32),
+               d = lane_value(v, 48);
+  const double ab = b > a ? b : a, cd = d > c ? d : c;
+  return cd > ab ? cd : ab;
+}
+
+// The best of the workgroup's candidates, in every thread (NaN norms never
+// win; col = -1 when there is none).  No candidate holds a NaN: cand_less
+// keeps them out.
+template <int NT>
+__device__ __forceinline__ QrCand cand_best(QrCand c, QrCand* sh) {
+  const double best = wave_max(c.norm);
+  unsigned long long at = __ballot(c.norm == best);
+  QrCand w = {best, 0, 0};
+  int l = __ffsll((long long)at) - 1;
+  w.pos = __builtin_amdgcn_readlane(c.pos, l);
+  w.col = __builtin_amdgcn_readlane(c.col, l);
+  for (at &= at - 1; at != 0; at &= at - 1) {  // a tie: the first place
+    l = __ffsll((long long)at) - 1;
+    const int pos = __builtin_amdgcn_readlane(c.pos, l);
+    if (pos < w.pos) {
+      w.pos = pos;
+      w.col = __builtin_amdgcn_readlane(c.col, l);
     }
   }
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = w;
+  __syncthreads();
+  c = sh[0];
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const double ob = __shfl_xor(best, off, 64);
-    const int oi = __shfl_xor(bidx, off, 64);
-    if (ob > best || (ob == best && oi < bidx)) {
-      best = ob;
-      bidx = oi;
-    }
-  }
-  if (lane == 0) {
-    bv[wid] = best;
-    bi[wid] = bidx;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    double b = bv[0];
-    int ix = bi[0];
-    for (int w = 1; w < 16; ++w)
-      if (bv[w] > b || (bv[w] == b && bi[w] < ix)) {
-        b = bv[w];
-        ix = bi[w];
-      }
-    bi[0] = ix;
-  }
-  __syncthreads();
-  const int p = bi[0] < m ? bi[0] : s;  // no column compares (NaN norms): keep s
-  __syncthreads();
-  if (p != s) {
-    for (int i = tid; i < k; i += 1024) {
-      const double t = A[(int64_t)s * k + i];
-      A[(int64_t)s * k + i] = A[(int64_t)p * k + i];
-      A[(int64_t)p * k + i] = t;
-    }
-    if (tid == 0) {
-      const double t = nrm[s];
-      nrm[s] = nrm[p];
-      nrm[p] = t;
-      const int q = perm[s];
-      perm[s] = perm[p];
-      perm[p] = q;
-    }
-  }
-  __syncthreads();
-  double* col = A + (int64_t)s * k;
-  double ss = 0.0;
-  for (int i = s + tid; i < k; i += 1024) ss += col[i] * col[i];
-  const double nx2 = block_sum_1024(ss, red);
-  if (tid == 0) {
-    const double x0 = col[s];
-    const double nx = sqrt(nx2);
-    if (nx == 0.0) {
-      sbeta = 0.0;
-      tau[0] = 0.0;
-      rdiag[s] = 0.0;
-      if (*info == 0) *info = s + 1;
-    } else {
-      const double beta = x0 >= 0.0 ? -nx : nx;
-      sbeta = beta;
-      tau[0] = (beta - x0) / beta;
-      rdiag[s] = beta;
-    }
-    sx0 = x0;
-  }
-  __syncthreads();
-  const double beta = sbeta, x0 = sx0;
-  for (int i = tid; i < k; i += 1024) {
-    double vi = 0.0;
-    if (i == s) vi = beta == 0.0 ? 0.0 : 1.0;
-    else if (i > s && beta != 0.0) vi = col[i] / (x0 - beta);
-    v[i] = vi;
-  }
+  for (int q = 1; q < NT / 64; ++q)
+    if (cand_less(c, sh[q])) c = sh[q];
+  return c;
 }
 
-// Step s, every column j > s: A[s:, j] -= tau v (v^T A[s:, j]); residual norm
-// over rows s+1.. recomputed.  One wave per column.
-__global__ __launch_bounds__(256) void k_qr_apply(int s, int m, int k, double* __restrict__ A,
-                                                  double* __restrict__ nrm,
-                                                  const double* __restrict__ v,
-                                                  const double* __restrict__ tau) {
-  const int j = s + 1 + blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (j >= m) return;
-  double* col = A + (int64_t)j * k;
-  const double t = tau[0];
-  double w = 0.0;
-  for (int i = s + lane; i < k; i += 64) w += v[i] * col[i];
-  w = wave_sum(w);
-  double r = 0.0;
-  for (int i = s + lane; i < k; i += 64) {
-    const double a = col[i] - t * v[i] * w;
-    col[i] = a;
-    if (i > s) r += a * a;
+constexpr int kQrThreads = 512;
+
+// A (point-major, column j = point points[j], k values at pitch kp = k rounded
+// up to even, zero beyond k), the places, and the candidates of the first step.
+__global__ __launch_bounds__(kQrThreads) void k_qr_gather(const double* __restrict__ phi,
+                                                          const int* __restrict__ points, int m,
+                                                          int k, int kp, int64_t npts,
+                                                          double* __restrict__ A,
+                                                          int* __restrict__ pos,
+                                                          int* __restrict__ perm,
+                                                          QrCand* __restrict__ cand) {
+  __shared__ QrCand sh[kQrThreads / 64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int waves = gridDim.x * (kQrThreads / 64);
+  QrCand best = {-1.0, m, -1};
+  for (int j = blockIdx.x * (kQrThreads / 64) + wave; j < m; j += waves) {
+    const int64_t pt = points ? (int64_t)points[j] : (int64_t)j;
+    double s = 0.0;
+#pragma unroll 4
+    for (int i = lane; i < kp; i += 64) {
+      const double v = i < k ? phi[(int64_t)i * npts + pt] : 0.0;
+      A[(int64_t)j * kp + i] = v;
+      s += v * v;
+    }
+    s = group_sum<64>(s);
+    if (lane == 0) pos[j] = perm[j] = j;
+    const QrCand c = {s, j, j};
+    if (cand_less(best, c)) best = c;
   }
-  r = wave_sum(r);
-  if (lane == 0) nrm[j] = r;
+  best = cand_best<kQrThreads>(best, sh);
+  if (threadIdx.x == 0) cand[blockIdx.x] = best;
 }
 
-__global__ void k_pivot_points(const int* __restrict__ perm, const int* __restrict__ points,
-                               int k, int* __restrict__ pivots) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= k) return;
-  pivots[j] = points ? points[perm[j]] : perm[j];
-}
-
-// Y[j][i] = phi_i(pivot_j) / ||.||_F ; state flags cleared
-__global__ __launch_bounds__(1024) void k_ns_init(const double* __restrict__ phi,
-                                                  const int* __restrict__ pivots, int k,
-                                                  int64_t npts, double* __restrict__ Y,
-                                                  int* __restrict__ state) {
-  __shared__ double red[16];
-  double s = 0.0;
-  for (int e = threadIdx.x; e < k * k; e += 1024) {
-    const int j = e / k, i = e % k;
-    const double x = phi[(int64_t)i * npts + pivots[j]];
-    Y[e] = x;
-    s += x * x;
+// Step s: pivot = the largest residual norm, first place on a tie;
+// (I - tau v v^T) A[s:, p] = beta e_s; every open column
+// A[s:, j] -= tau v (v^T A[s:, j]), its residual norm over rows s + 1 ...
+// recomputed; info = s + 1 on a zero column.
+// G lanes hold a column, two adjacent rows per lane in each of Q chunks of 2 G
+// rows (whole 128-byte lines per column from G = 8 on): 64 / G columns per
+// wave at a time, and a column's two sums cost log2(G) lane exchanges for all
+// of them at once.  Chunks above row s are left alone.
+template <int G, int Q>
+__global__ __launch_bounds__(kQrThreads) void k_qr_step(int s, int m, int k, int kp,
+                                                        double* __restrict__ A,
+                                                        int* __restrict__ pos,
+                                                        int* __restrict__ perm,
+                                                        const QrCand* __restrict__ cand,
+                                                        QrCand* __restrict__ next,
+                                                        const int* __restrict__ points,
+                                                        int* __restrict__ pivots,
+                                                        int* __restrict__ info) {
+  constexpr int C = 64 / G;  // columns per wave
+  static_assert(2 * G * Q <= kQrThreads, "a thread per row");
+  __shared__ QrCand sh[2][kQrThreads / 64];
+  __shared__ __align__(16) double sv[kQrThreads];
+  const int lane = threadIdx.x & 63, sub = lane % G;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int stride = gridDim.x * (kQrThreads / 64) * C;
+  // rows 2 sub + 2 G q and the next of column j
+  auto load = [&](double2* a, int j) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int row = 2 * (sub + G * q);
+      a[q] = double2{0.0, 0.0};
+      if (2 * G * (q + 1) > s && j < m && row < k)
+        a[q] = *reinterpret_cast<const double2*>(A + (int64_t)j * kp + row);
+    }
+  };
+  int j = (blockIdx.x * (kQrThreads / 64) + wave) * C + lane / G;
+  double2 a[Q];
+  load(a, j);  // in flight while the pivot is found
+  int pj = j < m ? pos[j] : -1;
+  QrCand c = {-1.0, m, -1};
+  if (threadIdx.x < gridDim.x) c = cand[threadIdx.x];  // one per workgroup, at most kQrThreads
+  c = cand_best<kQrThreads>(c, sh[0]);
+  const int cs = __builtin_amdgcn_readfirstlane(perm[s]);
+  // no column compares (NaN norms): the one at place s
+  const int cj = __builtin_amdgcn_readfirstlane(c.col < 0 ? cs : c.col);
+  const int p = __builtin_amdgcn_readfirstlane(c.col < 0 ? s : c.pos);
+  // the Householder vector: the column in every group of lanes for its norm
+  double2 v[Q];
+  load(v, cj);
+  const double xt = (int)threadIdx.x < k ? A[(int64_t)cj * kp + threadIdx.x] : 0.0;
+  double x0 = 0.0, nx2 = 0.0;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int row = 2 * (sub + G * q);
+    if (row < s) v[q].x = 0.0;
+    if (row + 1 < s) v[q].y = 0.0;
+    nx2 += v[q].x * v[q].x + v[q].y * v[q].y;
+    if (s / (2 * G) == q) x0 = lane_value(s & 1 ? v[q].y : v[q].x, (s / 2) % G);
   }
-  const double fro = sqrt(block_sum_1024(s, red));
+  const double nx = sqrt(group_sum<G>(nx2));
+  double tau = 0.0, beta = 0.0;
+  if (nx != 0.0) {
+    beta = x0 >= 0.0 ? -nx : nx;
+    tau = (beta - x0) / beta;
+  }
+  // one row per thread: a division takes about 40 instructions, and one per
+  // row in every wave was most of the step (14.5 us)
+  sv[threadIdx.x] = beta == 0.0 || (int)threadIdx.x < s ? 0.0
+                    : (int)threadIdx.x == s             ? 1.0
+                                                        : xt / (x0 - beta);
   __syncthreads();
-  const double inv = fro > 0.0 ? 1.0 / fro : 0.0;
-  for (int e = threadIdx.x; e < k * k; e += 1024) Y[e] *= inv;
-  if (threadIdx.x == 0) {
-    state[0] = 0;  // done: the products skip
-    state[1] = 0;  // polishing iterations taken
-    state[2] = 0;  // iterations taken
+#pragma unroll
+  for (int q = 0; q < Q; ++q) v[q] = *reinterpret_cast<const double2*>(&sv[2 * (sub + G * q)]);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    pivots[s] = points ? points[cj] : cj;
+    if (p != s) perm[p] = cs;  // place s is read by no later step, p > s
+    if (nx == 0.0 && *info == 0) *info = s + 1;
   }
+  QrCand best = {-1.0, m, -1};
+  while (j < m) {
+    // the open column at place s moves to the pivot's place
+    const int np = j == cj ? s : j == cs ? p : pj;
+    if (np != pj && sub == 0) pos[j] = np;
+    double w = 0.0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) w += v[q].x * a[q].x + v[q].y * a[q].y;
+    w = group_sum<G>(w);
+    double r = 0.0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int row = 2 * (sub + G * q);
+      a[q].x -= tau * v[q].x * w;
+      a[q].y -= tau * v[q].y * w;
+      if (2 * G * (q + 1) > s && np > s && row < k)
+        *reinterpret_cast<double2*>(A + (int64_t)j * kp + row) = a[q];
+      if (row > s) r += a[q].x * a[q].x;
+      if (row + 1 > s) r += a[q].y * a[q].y;
+    }
+    r = group_sum<G>(r);
+    const QrCand o = {r, np, j};
+    if (np > s && cand_less(best, o)) best = o;
+    j += stride;
+    if (j < m) {
+      load(a, j);
+      pj = pos[j];
+    }
+  }
+  best = cand_best<kQrThreads>(best, sh[1]);
+  if (threadIdx.x == 0) next[blockIdx.x] = best;
 }
 
-// err = max |G - I| with G = Y Y^T.  Below 1e-10 two more steps polish the
-// result (the iteration converges quadratically there); then done.
-__global__ __launch_bounds__(1024) void k_ns_update(double* __restrict__ Y,
-                                                    const double* __restrict__ G,
-                                                    const double* __restrict__ Z, int k,
-                                                    int* __restrict__ state) {
-  if (state[0] != 0) return;
-  __shared__ double red[16];
-  __shared__ int go;
+// ---- Newton-Schulz, two launches per iteration on 16 x 16 tiles, four waves
+// each, operands straight from the caches (k <= 512: at most 2 MB a matrix).
+// The general products took four launches per iteration (22 us at 128
+// orbitals); these two take 3.4 us each on average over the iterations that
+// work and those that find the iteration done.
+
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+// acc[i][j] = sum_t X[i0 + i][t] Z(t, j0 + j), Z(t, j) = TRANS ? Z[j][t] : Z[t][j],
+// over t in 16s from t0 in strides of dt
+template <bool TRANS>
+__device__ __forceinline__ d4 ns_tile(const double* X, const double* Z, int k, int i0, int j0,
+                                      int t0 = 0, int dt = 16) {
+  const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
+  const bool ri = i0 + li < k, rj = j0 + li < k;
+  const int64_t xo = (int64_t)min(i0 + li, k - 1) * k;
+  const int64_t zr = (int64_t)min(j0 + li, k - 1);
+  d4 acc[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) acc[u] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+  for (; t0 < k; t0 += dt) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int t = t0 + 4 * u + g, tc = min(t, k - 1);
+      const double x = X[xo + tc], z = TRANS ? Z[zr * k + tc] : Z[(int64_t)tc * k + zr];
+      acc[u] = __builtin_amdgcn_mfma_f64_16x16x4f64(ri && t < k ? x : 0.0,
+                                                    rj && t < k ? z : 0.0, acc[u], 0, 0, 0);
+    }
+  }
+  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+}
+
+// The same tile by four waves, a quarter of the sum each; the whole in wave 0.
+template <bool TRANS>
+__device__ __forceinline__ d4 ns_tile4(const double* X, const double* Z, int k, int i0, int j0,
+                                       d4 (*red)[64]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  d4 acc = ns_tile<TRANS>(X, Z, k, i0, j0, 16 * wave, 64);
+  if (wave > 0) red[wave - 1][lane] = acc;
+  __syncthreads();
+  if (wave == 0) acc = ((acc + red[0][lane]) + red[1][lane]) + red[2][lane];
+  return acc;
+}
+
+// Stores tile (i0, j0), i0 >= j0, of G = Y Y^T and its mirror image; the
+// tile's largest |G - I| in every lane (a NaN never compares).
+__device__ __forceinline__ double ns_gram_tile(d4 acc, double* G, int k, int i0, int j0) {
+  const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
   double e = 0.0;
-  for (int q = threadIdx.x; q < k * k; q += 1024) {
-    const int j = q / k, i = q % k;
-    const double d = fabs(G[q] - (i == j ? 1.0 : 0.0));
-    e = d > e ? d : e;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int i = i0 + g + 4 * v, j = j0 + li;
+    if (i < k && j < k) {
+      G[(int64_t)i * k + j] = acc[v];
+      if (i0 != j0) G[(int64_t)j * k + i] = acc[v];
+      const double d = fabs(acc[v] - (i == j ? 1.0 : 0.0));
+      e = d > e ? d : e;
+    }
   }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
     const double o = __shfl_xor(e, off, 64);
     e = o > e ? o : e;
   }
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = e;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double mx = 0.0;
-    for (int w = 0; w < 16; ++w) mx = red[w] > mx ? red[w] : mx;
-    int pol = state[1];
-    if (mx < 1e-10) ++pol;
-    go = pol <= 2;
-    state[1] = pol;
-    state[2] += 1;
+  return e;
+}
+
+// Yn = (3 Y - z) / 2, tile (i0, j0), z = G Y
+__device__ __forceinline__ void ns_step_tile(d4 z, const double* Y, double* Yn, int k, int i0,
+                                             int j0) {
+  const int lane = threadIdx.x & 63, li = lane & 15, g = lane >> 4;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int i = i0 + g + 4 * v, j = j0 + li;
+    if (i < k && j < k) Yn[(int64_t)i * k + j] = 1.5 * Y[(int64_t)i * k + j] - 0.5 * z[v];
   }
-  __syncthreads();
-  if (!go) {
-    if (threadIdx.x == 0) state[0] = 1;
+}
+
+// Below 1e-10 two more steps polish the result (the iteration converges
+// quadratically there): iteration it is the last one, taking no step, when
+// the errors of iterations 0 .. it hold a third value below it.
+__device__ __forceinline__ bool ns_done(const double* err, int it) {
+  const int lane = threadIdx.x & 63;
+  int below = 0;
+  for (int b = 0; b <= it; b += 64)
+    below += __popcll(__ballot(b + lane <= it && err[min(b + lane, it)] < 1e-10));
+  return below > 2;
+}
+
+// the largest of non-negative doubles: their bit patterns compare alike
+__device__ __forceinline__ void max_into(double* p, double v) {
+  atomicMax(reinterpret_cast<unsigned long long*>(p),
+            (unsigned long long)__double_as_longlong(v));
+}
+
+// Y[j][i] = phi_i(pivot_j), one workgroup per pivot, and the row's square sum
+__global__ __launch_bounds__(256) void k_ns_gather(const double* __restrict__ phi,
+                                                   const int* __restrict__ pivots, int k,
+                                                   int64_t npts, double* __restrict__ Y,
+                                                   double* __restrict__ sq) {
+  __shared__ double red[4];
+  const int j = blockIdx.x;
+  const int64_t pt = pivots[j];
+  double s = 0.0;
+  for (int i = threadIdx.x; i < k; i += 256) {
+    const double x = phi[(int64_t)i * npts + pt];
+    Y[(int64_t)j * k + i] = x;
+    s += x * x;
+  }
+  s = block_sum_1024(s, red);
+  if (threadIdx.x == 0) sq[j] = s;
+}
+
+// Y /= ||Y||_F (one workgroup per row); the iteration's state cleared
+__global__ __launch_bounds__(256) void k_ns_init(int k, const double* __restrict__ sq,
+                                                 double* __restrict__ Y, int iters,
+                                                 double* __restrict__ err,
+                                                 int* __restrict__ state) {
+  __shared__ double red[4];
+  double s = 0.0;
+  for (int i = threadIdx.x; i < k; i += 256) s += sq[i];
+  const double fro = sqrt(block_sum_1024(s, red));
+  const double inv = fro > 0.0 ? 1.0 / fro : 0.0;
+  for (int i = threadIdx.x; i < k; i += 256) Y[(int64_t)blockIdx.x * k + i] *= inv;
+  if (blockIdx.x == 0) {
+    for (int i = threadIdx.x; i < iters; i += 256) err[i] = 0.0;
+    if (threadIdx.x == 0) {
+      state[0] = 0;  // done: the launches below exit
+      state[1] = 0;  // which of the two buffers holds the result
+    }
+  }
+}
+
+// tile t of the lower triangle, row by row
+__device__ __forceinline__ void lower_tile(int t, int& i, int& j) {
+  i = 0;
+  while (t > i) t -= ++i;
+  j = t;
+}
+
+__global__ __launch_bounds__(256) void k_ns_gram(const double* __restrict__ Y,
+                                                double* __restrict__ G, int k, int it,
+                                                double* __restrict__ err,
+                                                const int* __restrict__ state) {
+  if (state[0] != 0) return;
+  __shared__ d4 red[3][64];
+  int i, j;
+  lower_tile(blockIdx.x, i, j);
+  const d4 acc = ns_tile4<true>(Y, Y, k, 16 * i, 16 * j, red);
+  if (threadIdx.x >= 64) return;
+  const double e = ns_gram_tile(acc, G, k, 16 * i, 16 * j);
+  if (threadIdx.x == 0) max_into(&err[it], e);
+}
+
+__global__ __launch_bounds__(256) void k_ns_step(const double* __restrict__ Y,
+                                                const double* __restrict__ G,
+                                                double* __restrict__ Yn, int k, int it,
+                                                const double* __restrict__ err,
+                                                int* __restrict__ state) {
+  // after the last iteration err stays 0, so every later launch ends here too
+  if (ns_done(err, it)) {
+    if (blockIdx.x == 0 && threadIdx.x == 0 && state[0] == 0) {
+      state[0] = 1;
+      state[1] = it & 1;
+    }
     return;
   }
-  for (int q = threadIdx.x; q < k * k; q += 1024) Y[q] = 1.5 * Y[q] - 0.5 * Z[q];
+  __shared__ d4 red[3][64];
+  const int T = (k + 15) / 16;
+  const int i0 = 16 * ((int)blockIdx.x / T), j0 = 16 * ((int)blockIdx.x % T);
+  const d4 z = ns_tile4<false>(G, Y, k, i0, j0, red);
+  if (threadIdx.x < 64) ns_step_tile(z, Y, Yn, k, i0, j0);
+}
+
+// Iterations it0 .. iters - 1 in one workgroup, for the rare matrix that the
+// launched iterations leave unfinished (a condition number above about 1e5);
+// exits at once otherwise.  Buffers and err are read and written by one
+// workgroup only, with a barrier between.
+__global__ __launch_bounds__(1024) void k_ns_tail(double* Y0, double* Y1, double* G, int k,
+                                                  int it0, int iters, double* err, int* state) {
+  if (state[0] != 0) return;
+  const int T = (k + 15) / 16, wave = threadIdx.x >> 6;
+  for (int it = it0; it < iters; ++it) {
+    double* Y = (it & 1) ? Y1 : Y0;
+    double* Yn = (it & 1) ? Y0 : Y1;
+    for (int t = wave; t < T * (T + 1) / 2; t += 16) {
+      int i, j;
+      lower_tile(t, i, j);
+      const double e =
+          ns_gram_tile(ns_tile<true>(Y, Y, k, 16 * i, 16 * j), G, k, 16 * i, 16 * j);
+      if ((threadIdx.x & 63) == 0) max_into(&err[it], e);
+    }
+    __threadfence();
+    __syncthreads();
+    // read past the caches, where the maxima were formed
+    int below = 0;
+    for (int q = 0; q <= it; ++q)
+      below += __hip_atomic_load(&err[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < 1e-10;
+    if (below > 2) {
+      if (threadIdx.x == 0) {
+        state[0] = 1;
+        state[1] = it & 1;
+      }
+      return;
+    }
+    for (int t = wave; t < T * T; t += 16)
+      ns_step_tile(ns_tile<false>(G, Y, k, 16 * (t / T), 16 * (t % T)), Y, Yn, k, 16 * (t / T),
+                   16 * (t % T));
+    __syncthreads();
+  }
 }
 
 __global__ void k_set_int(int* __restrict__ p, int v) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *p = v;
 }
 
-__global__ void k_ns_finish(const int* __restrict__ state, int k, int* __restrict__ info) {
+// the result into Y0; info = k + 1 if the iteration did not converge
+__global__ __launch_bounds__(256) void k_ns_finish(const int* __restrict__ state, int iters, int k,
+                                                   double* __restrict__ Y0,
+                                                   const double* __restrict__ Y1,
+                                                   int* __restrict__ info) {
+  const int which = state[0] != 0 ? state[1] : iters & 1;
+  if (which != 0)
+    for (int i = threadIdx.x; i < k; i += 256)
+      Y0[(int64_t)blockIdx.x * k + i] = Y1[(int64_t)blockIdx.x * k + i];
   if (threadIdx.x == 0 && blockIdx.x == 0 && *info == 0 && state[0] == 0) *info = k + 1;
 }
 
@@ -419,43 +674,68 @@ hipError_t launch_scdm_preselect(const double* phi, int n, int k, const double* 
   hipLaunchKernelGGL(k_sum2_final, dim3(1), dim3(256), 0, s, part, kScdmSumBlocks, npts, means);
   const int64_t nb = scdm_sel_blocks(npts);
   hipLaunchKernelGGL(k_sel_count, dim3((unsigned)nb), dim3(256), 0, s, rho, g, means, npts, cnt);
-  hipLaunchKernelGGL(k_sel_scan, dim3(1), dim3(64), 0, s, cnt, (int)nb, off, count);
+  hipLaunchKernelGGL(k_sel_scan, dim3(1), dim3(1024), 0, s, cnt, (int)nb, off, count);
   hipLaunchKernelGGL(k_sel_write, dim3((unsigned)nb), dim3(256), 0, s, rho, g, means, npts, off,
                      points);
   return hipGetLastError();
 }
 
+int scdm_qr_groups(int m) {
+  // a wave per eight columns, up to two workgroups per CU (a candidate per
+  // thread of a workgroup)
+  return std::max(1, std::min((m + 63) / 64, kQrThreads));
+}
+
+template <int G, int Q>
+static void qr_step(int s, int m, int k, double* A, int* pos, int* perm, const QrCand* cand,
+                    QrCand* next, const int* points, int* pivots, int* info, hipStream_t st) {
+  hipLaunchKernelGGL((k_qr_step<G, Q>), dim3(scdm_qr_groups(m)), dim3(kQrThreads), 0, st, s, m, k,
+                     scdm_qr_pitch(k), A, pos, perm, cand, next, points, pivots, info);
+}
+
 hipError_t launch_scdm_qr(const double* phi, const int* points, int m, int k, int64_t npts,
-                          double* A, double* nrm, int* perm, double* v, double* tau,
-                          double* rdiag, int* pivots, int* info, hipStream_t s) {
-  hipLaunchKernelGGL(k_qr_gather, dim3((unsigned)((m + 3) / 4)), dim3(256), 0, s, phi, points, m,
-                     k, npts, A, nrm, perm);
+                          double* A, int* pos, int* perm, void* cand, int* pivots, int* info,
+                          hipStream_t s) {
+  const int groups = scdm_qr_groups(m);
+  QrCand* c[2] = {static_cast<QrCand*>(cand), static_cast<QrCand*>(cand) + groups};
+  hipLaunchKernelGGL(k_qr_gather, dim3(groups), dim3(kQrThreads), 0, s, phi, points, m, k,
+                     scdm_qr_pitch(k), npts, A, pos, perm, c[0]);
   for (int st = 0; st < k; ++st) {
-    hipLaunchKernelGGL(k_qr_pivot, dim3(1), dim3(1024), 0, s, st, m, k, A, nrm, perm, v, tau,
-                       rdiag, info);
-    const int rest = m - st - 1;
-    if (rest > 0)
-      hipLaunchKernelGGL(k_qr_apply, dim3((unsigned)((rest + 3) / 4)), dim3(256), 0, s, st, m, k,
-                         A, nrm, v, tau);
+    const QrCand* in = c[st & 1];
+    QrCand* out = c[(st + 1) & 1];
+    // up to 16 values of a column per lane: the registers of two columns (the
+    // Householder vector's and the wave's own) leave four waves per SIMD
+    if (k <= 32) qr_step<8, 2>(st, m, k, A, pos, perm, in, out, points, pivots, info, s);
+    else if (k <= 64) qr_step<8, 4>(st, m, k, A, pos, perm, in, out, points, pivots, info, s);
+    else if (k <= 128) qr_step<8, 8>(st, m, k, A, pos, perm, in, out, points, pivots, info, s);
+    else if (k <= 256) qr_step<16, 8>(st, m, k, A, pos, perm, in, out, points, pivots, info, s);
+    else if (k <= 512) qr_step<32, 8>(st, m, k, A, pos, perm, in, out, points, pivots, info, s);
+    else return hipErrorInvalidValue;
   }
-  hipLaunchKernelGGL(k_pivot_points, dim3((unsigned)((k + 255) / 256)), dim3(256), 0, s, perm,
-                     points, k, pivots);
   return hipGetLastError();
 }
 
+// Iterations issued as launches; the rest, up to max_iter, in k_ns_tail.
+// From Y = A / ||A||_F the smallest singular value grows by 1.5 per iteration
+// until it nears 1: 40 iterations reach a condition number of about 1e5.
+constexpr int kNsLaunched = 40;
+
 hipError_t launch_scdm_polar(const double* phi, const int* pivots, int k, int64_t npts, double* Y,
-                             double* G, double* Z, double* partial, int nsplit, int* state,
-                             int* info, int max_iter, hipStream_t s) {
-  hipLaunchKernelGGL(k_ns_init, dim3(1), dim3(1024), 0, s, phi, pivots, k, npts, Y, state);
-  hipError_t e = hipSuccess;
-  for (int it = 0; it < max_iter; ++it) {
-    e = launch_gemm_abt(Y, Y, k, k, k, 1.0, G, partial, nsplit, false, state, s);
-    if (e != hipSuccess) return e;
-    e = launch_gemm_ab(G, Y, k, k, k, 1.0, Z, false, state, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_ns_update, dim3(1), dim3(1024), 0, s, Y, G, Z, k, state);
+                             double* G, double* Z, double* sq, double* err, int* state, int* info,
+                             int max_iter, hipStream_t s) {
+  const int T = (k + 15) / 16;
+  hipLaunchKernelGGL(k_ns_gather, dim3(k), dim3(256), 0, s, phi, pivots, k, npts, Y, sq);
+  hipLaunchKernelGGL(k_ns_init, dim3(k), dim3(256), 0, s, k, sq, Y, max_iter, err, state);
+  const int launched = std::min(kNsLaunched, max_iter);
+  for (int it = 0; it < launched; ++it) {
+    double* in = (it & 1) ? Z : Y;
+    double* out = (it & 1) ? Y : Z;
+    hipLaunchKernelGGL(k_ns_gram, dim3(T * (T + 1) / 2), dim3(256), 0, s, in, G, k, it, err, state);
+    hipLaunchKernelGGL(k_ns_step, dim3(T * T), dim3(256), 0, s, in, G, out, k, it, err, state);
   }
-  hipLaunchKernelGGL(k_ns_finish, dim3(1), dim3(64), 0, s, state, k, info);
+  hipLaunchKernelGGL(k_ns_tail, dim3(1), dim3(1024), 0, s, Y, Z, G, k, launched, max_iter, err,
+                     state);
+  hipLaunchKernelGGL(k_ns_finish, dim3(k), dim3(256), 0, s, state, max_iter, k, Y, Z, info);
   return hipGetLastError();
 }
 
