@@ -137,8 +137,7 @@ int ace_apply_noalloc(const ace_plan *plan, void *stream, const double *xi, cons
  *   ex      device double output.
  *   pair_e  NULL, or device [n_orb][n_orb] double: entry (i, j), i <= j, gets
  *           that pair's share -alpha (2 - delta_ij) (ij|ji); other entries are
- *           left untouched.  Requesting pair_e solves one pair per transform
- *           instead of two. */
+ *           left untouched.  Two pairs share a transform in either case. */
 int exx_energy(const ace_plan *plan, void *stream, void *ws, size_t ws_bytes, const double *phi,
                const uint8_t *pair_mask, double *ex, double *pair_e);
 

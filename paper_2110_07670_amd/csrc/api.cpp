@@ -167,7 +167,7 @@ void layout(ace_plan* p) {
   p->s_grid_bytes = align256((size_t)p->npts * 2 * bulk);
   p->max_pack_tile = (B * B + 1) / 2;
   p->nsplit = acex::gemm_abt_splits(p->n_orb, p->n_orb, p->npts);
-  p->eparts = acex::energy_parts_per_pack(p->n);
+  p->eparts = std::max(acex::energy_parts_per_pack(p->n), 2 * acex::pair_energy_parts(p->n));
   size_t off = 0;
   p->off_tab = off;
   p->tab_bytes = align256((size_t)ntiles * 2 * B * sizeof(int)) +
@@ -199,7 +199,7 @@ void layout(ace_plan* p) {
   p->off_epart = off;
   off += align256((size_t)p->max_pack_tile * p->eparts * sizeof(double));
   p->off_epack = off;
-  off += align256((size_t)npair * sizeof(double));
+  off += align256((size_t)2 * npair * sizeof(double));
   p->total = off;
 }
 
@@ -375,7 +375,7 @@ void build_schedule(const ace_plan* p, const uint8_t* mask, std::vector<Pack>& p
             code = a | (b << 8);
             half = 1;
           } else {
-            cur.c = i;
+            cur.e = acex::kPackUnit;
             cur.d = j;
             packs.push_back(cur);
             meta.push_back(code | (a << 16) | (b << 24));
@@ -403,51 +403,48 @@ void build_schedule(const ace_plan* p, const uint8_t* mask, std::vector<Pack>& p
   }
 }
 
-// Energy schedule: off-diagonal pairs (i, j), (i, j') of one row share a
-// transform (both halves then carry the weight 2); diagonal pairs are
-// single-pair transforms.  One pair per transform when per-pair energies are
-// wanted.
-void build_energy_schedule(const ace_plan* p, const uint8_t* mask, bool single,
-                           std::vector<Pack>& packs, std::vector<double>& weight,
-                           std::vector<int>& code) {
-  const int k = p->n_orb;
+// Energy schedule: the pairs tile by tile as in a build, so that a launch reads
+// two blocks of orbitals and not whole rows (96^3 FP64, 128 orbitals: 463
+// against 552 us per 128 transforms); launches are runs of tiles, `first`
+// their first packs.  Two pairs (i, j), (i, j') of one tile row share a
+// transform.  E_x alone (`code` null): off-diagonal pairs share one (both
+// halves carry weight 2), diagonal pairs go alone.  Every pair's energy
+// wanted: the diagonal pair shares one too, and code[2 p], code[2 p + 1] =
+// i n_orb + j of pack p's pairs (-1: none).
+void build_energy_schedule(const ace_plan* p, const uint8_t* mask, std::vector<Pack>& packs,
+                           std::vector<double>& weight, std::vector<int>* code,
+                           std::vector<int>& first) {
+  const int k = p->n_orb, B = p->block, nb = (k + B - 1) / B;
   packs.clear();
   weight.clear();
-  code.clear();
-  for (int i = 0; i < k; ++i) {
-    if (mask_on(mask, k, i, i)) {
-      packs.push_back(Pack{i, i, -1, -1});
-      weight.push_back(-p->alpha);
-      code.push_back(i * k + i);
-    }
-    int half = 0;
-    Pack cur{-1, -1, -1, -1};
-    for (int j = i + 1; j < k; ++j) {
-      if (!mask_on(mask, k, i, j)) continue;
-      if (single) {
-        packs.push_back(Pack{i, j, -1, -1});
-        weight.push_back(-2.0 * p->alpha);
-        code.push_back(i * k + j);
-        continue;
+  first.assign(1, 0);
+  for (int I = 0; I < nb; ++I)
+    for (int J = I; J < nb; ++J) {
+      const size_t tile0 = packs.size();
+      for (int i = I * B; i < std::min(k, (I + 1) * B); ++i) {
+        bool open = false;
+        for (int j = std::max(i, J * B); j < std::min(k, (J + 1) * B); ++j) {
+          if (!mask_on(mask, k, i, j)) continue;
+          if (open) {
+            packs.back().e = acex::kPackUnit;
+            packs.back().d = j;
+            if (code) code->back() = i * k + j;
+            open = false;
+            continue;
+          }
+          packs.push_back(Pack{i, j, -1, -1});
+          if (code) {
+            code->push_back(i * k + j);
+            code->push_back(-1);
+          } else {
+            weight.push_back((i == j ? -1.0 : -2.0) * p->alpha);
+          }
+          open = code || i != j;
+        }
       }
-      if (half == 0) {
-        cur = Pack{i, j, -1, -1};
-        half = 1;
-      } else {
-        cur.c = i;
-        cur.d = j;
-        packs.push_back(cur);
-        weight.push_back(-2.0 * p->alpha);
-        code.push_back(-1);
-        half = 0;
-      }
+      if (packs.size() - first.back() > (size_t)p->max_pack_tile) first.push_back((int)tile0);
     }
-    if (half == 1) {
-      packs.push_back(cur);
-      weight.push_back(-2.0 * p->alpha);
-      code.push_back(-1);
-    }
-  }
+  first.push_back((int)packs.size());
 }
 
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
@@ -961,31 +958,30 @@ int exx_energy(const ace_plan* p, void* stream, void* ws, size_t ws_bytes, const
   hipError_t e;
   std::vector<Pack> packs;
   std::vector<double> weight;
-  std::vector<int> code;
-  build_energy_schedule(p, pair_mask, pair_e != nullptr, packs, weight, code);
+  std::vector<int> code, first;
+  build_energy_schedule(p, pair_mask, packs, weight, pair_e ? &code : nullptr, first);
   const int np = (int)packs.size();
   const size_t bulk = p->prec == 0 ? 8 : 4;
   const size_t o_packs = 0;
   const size_t o_tw = o_packs + align256(std::max<size_t>(np, 1) * sizeof(Pack));
   const size_t o_w = o_tw + align256((size_t)p->n * 2 * bulk);
-  const size_t o_code = o_w + align256(std::max<size_t>(np, 1) * sizeof(double));
-  const size_t tab_used = o_code + align256(std::max<size_t>(np, 1) * sizeof(int));
+  const size_t o_code = o_w + align256(std::max<size_t>(weight.size(), 1) * sizeof(double));
+  const size_t tab_used = o_code + align256(std::max<size_t>(code.size(), 1) * sizeof(int));
   if (tab_used > p->tab_bytes) return ACE_ERR_SIZE;
   std::vector<unsigned char> host(tab_used, 0);
-  if (np) {
-    std::memcpy(host.data() + o_packs, packs.data(), (size_t)np * sizeof(Pack));
-    std::memcpy(host.data() + o_w, weight.data(), (size_t)np * sizeof(double));
-    std::memcpy(host.data() + o_code, code.data(), (size_t)np * sizeof(int));
-  }
+  if (np) std::memcpy(host.data() + o_packs, packs.data(), (size_t)np * sizeof(Pack));
+  if (!weight.empty())
+    std::memcpy(host.data() + o_w, weight.data(), weight.size() * sizeof(double));
+  if (!code.empty()) std::memcpy(host.data() + o_code, code.data(), code.size() * sizeof(int));
   std::memcpy(host.data() + o_tw, p->tw_host.data(), p->tw_host.size());
   {
     ProfScope ps(p, 7, s);
     e = hipMemcpyAsync(w + p->off_tab, host.data(), tab_used, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_fail(e);
   }
-  const Pack* d_packs = reinterpret_cast<const Pack*>(w + p->off_tab + o_packs);
+  Pack* d_packs = reinterpret_cast<Pack*>(w + p->off_tab + o_packs);
   const double* d_w = reinterpret_cast<const double*>(w + p->off_tab + o_w);
-  const int* d_code = reinterpret_cast<const int*>(w + p->off_tab + o_code);
+  int* d_code = reinterpret_cast<int*>(w + p->off_tab + o_code);
   acex::GridArgs g;
   g.n = p->n;
   g.prec = p->prec;
@@ -1006,34 +1002,48 @@ int exx_energy(const ace_plan* p, void* stream, void* ws, size_t ws_bytes, const
   double* epart = reinterpret_cast<double*>(w + p->off_epart);
   double* epack = reinterpret_cast<double*>(w + p->off_epack);
   const double factor = p->omega / ((double)p->npts * (double)p->npts);
-  const int chunk = p->max_pack_tile;
-  for (int c0 = 0; c0 < np; c0 += chunk) {
-    const int cnt = std::min(chunk, np - c0);
+  const bool zxy = acex::energy_zxy(p->n, p->prec);
+  const int parts = pair_e ? acex::pair_energy_parts(p->n) : acex::energy_parts_per_pack(p->n);
+  if (pair_e && np) {
+    // the pairs' overlap integrals (in the Cholesky factor's place)
+    ProfScope ps(p, 7, s);
+    double* ov = reinterpret_cast<double*>(w + p->off_L);
+    e = acex::launch_gemm_abt(phi, phi, p->n_orb, p->n_orb, p->npts, p->dV, ov,
+                              reinterpret_cast<double*>(w + p->off_part), p->nsplit, true,
+                              nullptr, s);
+    if (e != hipSuccess) return hip_fail(e);
+    e = acex::launch_pair_scale(d_packs, d_code, np, ov, p->n_orb, p->prec, s);
+    if (e != hipSuccess) return hip_fail(e);
+  }
+  for (size_t l = 0; l + 1 < first.size(); ++l) {
+    const int c0 = first[l], cnt = first[l + 1] - c0;
     {
       ProfScope ps(p, 0, s);
-      e = acex::launch_fwd_yz(g, phi_bulk, d_packs + c0, cnt, S, s);
+      e = acex::launch_fwd_yz(g, phi_bulk, d_packs + c0, cnt, S, s, zxy);
       if (e != hipSuccess) return hip_fail(e);
     }
     {
       ProfScope ps(p, 9, s);
-      e = acex::launch_energy_x(g, S, cnt, epart, s);
-      if (e != hipSuccess) return hip_fail(e);
-      e = acex::launch_energy_reduce(epart, cnt, p->eparts, factor, epack + c0, s);
+      if (pair_e) {
+        e = acex::launch_pair_energy_x(g, S, cnt, epart, zxy, s);
+        if (e != hipSuccess) return hip_fail(e);
+        e = acex::launch_pair_energy_reduce(epart, d_packs + c0, cnt, parts, factor,
+                                            epack + 2 * (size_t)c0, s);
+      } else {
+        e = acex::launch_energy_x(g, S, cnt, epart, zxy, s);
+        if (e != hipSuccess) return hip_fail(e);
+        e = acex::launch_energy_reduce(epart, cnt, parts, factor, epack + c0, s);
+      }
       if (e != hipSuccess) return hip_fail(e);
     }
   }
   ProfScope ps(p, 7, s);
-  if (np == 0) {
-    e = acex::launch_fill_f64(ex, 0.0, 1, s);
-  } else {
+  if (np == 0) e = acex::launch_fill_f64(ex, 0.0, 1, s);
+  else if (pair_e)
+    e = acex::launch_pair_energies(epack, d_code, 2 * np, p->n_orb, -p->alpha, ex, pair_e, s);
+  else
     e = acex::launch_weighted_sum(epack, d_w, np, ex, s);
-  }
-  if (e != hipSuccess) return hip_fail(e);
-  if (pair_e && np) {
-    e = acex::launch_scatter_pair_energies(epack, d_code, np, p->n_orb, -p->alpha, pair_e, s);
-    if (e != hipSuccess) return hip_fail(e);
-  }
-  return ACE_OK;
+  return e == hipSuccess ? ACE_OK : hip_fail(e);
 }
 
 int ace_wannier(const ace_plan* p, void* stream, const double* phi, double* z, double* feat) {

@@ -826,22 +826,44 @@ hipError_t launch_weighted_sum(const double* e, const double* w, int count, doub
   return hipGetLastError();
 }
 
-// pair_e[i][j] = weight * e_pack[p] for packs carrying one pair (i, j)
-__global__ void k_scatter_pairs(const double* __restrict__ e_pack, const int* __restrict__ pair_of_pack,
-                                int npack, int n_orb, double wscale, double* __restrict__ pair_e) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= npack) return;
-  const int code = pair_of_pack[p];
-  const int i = code / n_orb, j = code % n_orb;
-  pair_e[(int64_t)i * n_orb + j] = wscale * (i == j ? 1.0 : 2.0) * e_pack[p];
+__device__ __forceinline__ double pair_weight(int code, int n_orb, double wscale) {
+  return wscale * (code / n_orb == code % n_orb ? 1.0 : 2.0);
 }
 
-hipError_t launch_scatter_pair_energies(const double* e_pack, const int* pair_of_pack, int npack,
-                                        int n_orb, double weight_scale, double* pair_e,
-                                        hipStream_t s) {
-  if (npack <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_scatter_pairs, dim3((npack + 255) / 256), dim3(256), 0, s, e_pack,
-                     pair_of_pack, npack, n_orb, weight_scale, pair_e);
+// sum of w e in a fixed order: 1024 interleaved runs, then a tree over them
+__global__ __launch_bounds__(1024) void k_pair_sum(const double* __restrict__ e,
+                                                   const int* __restrict__ codes, int count,
+                                                   int n_orb, double wscale,
+                                                   double* __restrict__ out) {
+  __shared__ double part[1024];
+  const int tid = threadIdx.x;
+  double s = 0.0;
+#pragma unroll 4
+  for (int i = tid; i < count; i += 1024)
+    if (codes[i] >= 0) s += pair_weight(codes[i], n_orb, wscale) * e[i];
+  part[tid] = s;
+  for (int d = 512; d >= 1; d /= 2) {
+    __syncthreads();
+    if (tid < d) part[tid] += part[tid + d];
+  }
+  if (tid == 0) *out = part[0];
+}
+
+__global__ void k_scatter_pairs(const double* __restrict__ e, const int* __restrict__ codes,
+                                int count, int n_orb, double wscale,
+                                double* __restrict__ pair_e) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= count || codes[i] < 0) return;
+  pair_e[codes[i]] = pair_weight(codes[i], n_orb, wscale) * e[i];
+}
+
+hipError_t launch_pair_energies(const double* e, const int* codes, int count, int n_orb,
+                                double weight_scale, double* ex, double* pair_e, hipStream_t s) {
+  if (count <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_pair_sum, dim3(1), dim3(1024), 0, s, e, codes, count, n_orb, weight_scale,
+                     ex);
+  hipLaunchKernelGGL(k_scatter_pairs, dim3((count + 255) / 256), dim3(256), 0, s, e, codes, count,
+                     n_orb, weight_scale, pair_e);
   return hipGetLastError();
 }
 

@@ -8,11 +8,13 @@
 
 namespace acex {
 
-// One packed transform carries two real pairs: rho = phi_a phi_b + i phi_c phi_d.
-// c = d = -1 marks a transform carrying a single pair.
+// One packed transform carries two real pairs that share their first orbital,
+// rho = phi_a (phi_b + i 2^(e - kPackUnit) phi_d); e = -1 marks a transform
+// carrying the pair (a, b) alone.
 struct Pack {
-  int a, b, c, d;
+  int a, b, e, d;
 };
+constexpr int kPackUnit = 1024;
 
 struct GridArgs {
   int n;              // points per axis (cubic grid)
@@ -65,8 +67,24 @@ hipError_t launch_zinv_acc(const GridArgs& g, int block, bool diag, const void* 
 hipError_t launch_poisson_x(const GridArgs& g, void* S, int npack, hipStream_t s);
 // x forward transform and sum of K |Z|^2 per workgroup into part[npack][parts_per_pack].
 hipError_t launch_energy_x(const GridArgs& g, const void* S, int npack, double* part,
-                           hipStream_t s);
+                           bool zxy, hipStream_t s);
+// zxy: S is laid out as launch_fwd_yz's zxy form.
 int energy_parts_per_pack(int n);
+// The layout of S for the energy passes: zxy where the forward pass of this
+// grid writes it.
+bool energy_zxy(int n, int prec);
+// The energies of both pairs of every transform, apart: x forward transform
+// and, with Z = A + i B, A and B the transforms of the two real pair densities,
+// the sums of K |A|^2 and K |B|^2 per workgroup into
+// part[npack][2][pair_energy_parts(n)].
+int pair_energy_parts(int n);
+hipError_t launch_pair_energy_x(const GridArgs& g, const void* S, int npack, double* part,
+                                bool zxy, hipStream_t s);
+// Sets each pack's scale from the pairs' overlap integrals ov [n_orb][n_orb]:
+// the pair with the larger one first (codes, two per pack, swap along), the
+// other scaled up by the power of two that brings it level.
+hipError_t launch_pair_scale(Pack* packs, int* codes, int npack, const double* ov, int n_orb,
+                             int prec, hipStream_t s);
 // Inverse (y,z) transforms back to real space, natural order, in place.
 hipError_t launch_inv_yz(const GridArgs& g, void* S, int npack, hipStream_t s);
 
@@ -118,6 +136,10 @@ hipError_t launch_fill_i32(int* p, int v, int64_t count, hipStream_t s);
 // e_pack[p] = sum of the parts of pack p (fixed order) * omega / N^2.
 hipError_t launch_energy_reduce(const double* part, int npack, int parts, double factor,
                                 double* e_pack, hipStream_t s);
+// The same for launch_pair_energy_x: e[2 p], e[2 p + 1] the two pairs of pack p
+// (the second's scale divided out).
+hipError_t launch_pair_energy_reduce(const double* part, const Pack* packs, int npack, int parts,
+                                     double factor, double* e, hipStream_t s);
 
 // Small utility kernels.
 hipError_t launch_fill_f64(double* p, double v, int64_t count, hipStream_t s);
@@ -143,9 +165,10 @@ hipError_t launch_trace(const double* M, int n, double* out, hipStream_t s);
 // out = sum_i w[i] e[i] in a fixed order (single workgroup)
 hipError_t launch_weighted_sum(const double* e, const double* w, int count, double* out,
                                hipStream_t s);
-hipError_t launch_scatter_pair_energies(const double* e_pack, const int* pair_of_pack,
-                                        int npack, int n_orb, double weight_scale,
-                                        double* pair_e, hipStream_t s);
+// ex = sum of w e over the pairs with code >= 0 (code = i n_orb + j, i <= j;
+// w = weight_scale (2 - delta_ij)) in a fixed order; pair_e[code] = w e.
+hipError_t launch_pair_energies(const double* e, const int* codes, int count, int n_orb,
+                                double weight_scale, double* ex, double* pair_e, hipStream_t s);
 
 // Pair screening (screen.hip): Berry-phase moments z[orb][6], Wannier
 // features feat[orb][4] = (centre xyz, spread), MLP pair predictions.
