@@ -55,6 +55,7 @@ struct Tile {
   int pack0, npack;
   unsigned useI, useJ;  // local orbitals with at least one kept pair
   bool complete;        // every pair of the tile kept: canonical pack order
+  int group0, ngroup;   // its transforms in groups of rows (incomplete or partial tiles)
 };
 
 struct ProfRec {
@@ -92,8 +93,8 @@ struct ace_plan {
 
 namespace {
 struct BuildTables {
-  std::vector<unsigned char> host;  // packs | meta | twiddles | tile orbitals
-  size_t o_packs = 0, o_meta = 0, o_tw = 0, o_orbs = 0, used = 0;
+  std::vector<unsigned char> host;  // packs | meta | twiddles | tile orbitals | groups
+  size_t o_packs = 0, o_meta = 0, o_tw = 0, o_orbs = 0, o_groups = 0, used = 0;
   std::vector<Tile> tiles;
   bool masked = false;
 };
@@ -173,7 +174,8 @@ void layout(ace_plan* p) {
   p->tab_bytes = align256((size_t)ntiles * 2 * B * sizeof(int)) +
                  align256((size_t)npair * sizeof(Pack)) + align256((size_t)npair * sizeof(int)) +
                  align256((size_t)p->n * 2 * bulk) + align256((size_t)npair * sizeof(int)) +
-                 align256((size_t)npair * sizeof(double));
+                 align256((size_t)npair * sizeof(double)) +
+                 align256((size_t)ntiles * B * sizeof(acex::TileGroup));
   off += align256(p->tab_bytes);
   p->off_phi32 = off;
   if (p->prec == 1) off += align256((size_t)p->n_orb * p->npts * sizeof(float));
@@ -338,8 +340,33 @@ std::vector<std::pair<int, int>> tile_order(int nb, bool last_full, bool paired)
   return out;
 }
 
+// Groups of whole rows (at most TileGroup::kRows and B / 2 transforms) of the
+// transforms with codes meta[0 .. npack - 1], for the fused pass of a tile
+// with pairs missing.
+void row_groups(const int* meta, int npack, int B, std::vector<acex::TileGroup>& out) {
+  acex::TileGroup g{};
+  for (int p = 0; p < npack;) {
+    const int a = meta[p] & 255;
+    unsigned mask = 0;
+    int e = p;
+    for (; e < npack && (meta[e] & 255) == a; ++e) {
+      mask |= 1u << ((meta[e] >> 8) & 255);
+      if (((meta[e] >> 16) & 255) != 255) mask |= 1u << ((meta[e] >> 24) & 255);
+    }
+    if (g.rows() == acex::TileGroup::kRows || g.count() + (e - p) > B / 2) {
+      if (g.rows() > 0) out.push_back(g);
+      g = acex::TileGroup{};
+      g.first_ = p;
+    }
+    g.add(a, e - p, mask);
+    p = e;
+  }
+  if (g.rows() > 0) out.push_back(g);
+}
+
 void build_schedule(const ace_plan* p, const uint8_t* mask, std::vector<Pack>& packs,
-                    std::vector<int>& meta, std::vector<int>& orbs, std::vector<Tile>& tiles) {
+                    std::vector<int>& meta, std::vector<int>& orbs, std::vector<Tile>& tiles,
+                    std::vector<acex::TileGroup>& groups) {
   const int B = p->block, k = p->n_orb;
   const int nb = (k + B - 1) / B;
   const std::vector<int> ord = pair_order(k, B, mask);
@@ -347,6 +374,7 @@ void build_schedule(const ace_plan* p, const uint8_t* mask, std::vector<Pack>& p
   tiles.clear();
   meta.clear();
   orbs.clear();
+  groups.clear();
   for (const auto& IJ : tile_order(nb, k % B == 0, p->prec == ACE_FP32)) {
     {
       const int I = IJ.first, J = IJ.second;
@@ -391,6 +419,10 @@ void build_schedule(const ace_plan* p, const uint8_t* mask, std::vector<Pack>& p
       }
       t.npack = local;
       t.complete = kept == (t.diag ? t.bi * (t.bi + 1) / 2 : t.bi * t.bj);
+      t.group0 = (int)groups.size();
+      if (!(t.complete && t.bi == B && t.bj == B))
+        row_groups(meta.data() + t.pack0, local, B, groups);
+      t.ngroup = (int)groups.size() - t.group0;
       if (t.npack > 0) {
         tiles.push_back(t);
         for (int a = 0; a < B; ++a) orbs.push_back(a < t.bi ? ord[t.i0 + a] : -1);
@@ -509,14 +541,16 @@ int prepare_tables(const ace_plan* p, const uint8_t* pair_mask, BuildTables& bt)
   std::vector<Pack> packs;
   std::vector<int> meta;
   std::vector<int> orbs;
-  build_schedule(p, pair_mask, packs, meta, orbs, bt.tiles);
+  std::vector<acex::TileGroup> groups;
+  build_schedule(p, pair_mask, packs, meta, orbs, bt.tiles, groups);
   bt.masked = pair_mask != nullptr;
   const size_t bulk = p->prec == 0 ? 8 : 4;
   bt.o_packs = 0;
   bt.o_meta = bt.o_packs + align256(std::max<size_t>(packs.size(), 1) * sizeof(Pack));
   bt.o_tw = bt.o_meta + align256(std::max<size_t>(meta.size(), 1) * sizeof(int));
   bt.o_orbs = bt.o_tw + align256((size_t)p->n * 2 * bulk);
-  bt.used = bt.o_orbs + align256(std::max<size_t>(orbs.size(), 1) * sizeof(int));
+  bt.o_groups = bt.o_orbs + align256(std::max<size_t>(orbs.size(), 1) * sizeof(int));
+  bt.used = bt.o_groups + align256(std::max<size_t>(groups.size(), 1) * sizeof(acex::TileGroup));
   if (bt.used > p->tab_bytes) return ACE_ERR_SIZE;
   bt.host.assign(bt.used, 0);
   if (!packs.empty())
@@ -524,6 +558,9 @@ int prepare_tables(const ace_plan* p, const uint8_t* pair_mask, BuildTables& bt)
   if (!meta.empty()) std::memcpy(bt.host.data() + bt.o_meta, meta.data(), meta.size() * sizeof(int));
   std::memcpy(bt.host.data() + bt.o_tw, p->tw_host.data(), p->tw_host.size());
   if (!orbs.empty()) std::memcpy(bt.host.data() + bt.o_orbs, orbs.data(), orbs.size() * sizeof(int));
+  if (!groups.empty())
+    std::memcpy(bt.host.data() + bt.o_groups, groups.data(),
+                groups.size() * sizeof(acex::TileGroup));
   return ACE_OK;
 }
 
@@ -547,6 +584,7 @@ struct BuildCtx {
   const Pack* d_packs = nullptr;
   const int* d_meta = nullptr;
   const int* d_orbs = nullptr;
+  const acex::TileGroup* d_groups = nullptr;
   bool three_ok = false, rows_ok = false;
 };
 
@@ -561,6 +599,7 @@ int build_begin(const ace_plan* p, hipStream_t s, char* w, const double* phi,
   c.d_packs = reinterpret_cast<const Pack*>(w + p->off_tab + bt.o_packs);
   c.d_meta = reinterpret_cast<const int*>(w + p->off_tab + bt.o_meta);
   c.d_orbs = reinterpret_cast<const int*>(w + p->off_tab + bt.o_orbs);
+  c.d_groups = reinterpret_cast<const acex::TileGroup*>(w + p->off_tab + bt.o_groups);
   acex::GridArgs& g = c.g;
   g.n = p->n;
   g.prec = p->prec;
@@ -594,20 +633,33 @@ bool tile_batch_whole(const ace_plan* p, const Tile& t) {
          t.bj == B && t.complete && (p->chunk == 0 || p->chunk >= t.npack);
 }
 
+// Is tile ti a full block x block tile with every pair kept (masked builds
+// too) that takes the fused inverse-z/W pass?
+bool tile_fused(const BuildCtx& c, size_t ti) {
+  const Tile& t = c.bt->tiles[ti];
+  const int B = c.p->block;
+  return (c.three_ok || c.rows_ok) && t.bi == B && t.bj == B && t.complete;
+}
+
+// Does it take three passes as a partial or masked tile?
+bool tile_list(const BuildCtx& c, size_t ti) {
+  return c.three_ok && !tile_fused(c, ti) &&
+         acex::list_ok(c.p->n, c.p->prec, c.p->block, c.bt->tiles[ti].complete);
+}
+
 // A1-A4 for tile ti: pair densities and Poisson solves into scratch S
 // (forward and middle passes; four-pass tiles also x and the inverse y/z).
-// Full tiles take three passes where the kernels fit (the inverse z
-// transform then feeds the W update directly); the others take four.
+// Three passes where the kernels fit (the inverse z transform then feeds the W
+// update directly), four elsewhere; a tile with pairs missing takes four on the
+// row-fused grids, where the W traffic of its few transforms bounds the update
+// either way (144^3 FP32, 256 orbitals screened: 125 ms fused, 124 not).
 int tile_transforms(const BuildCtx& c, hipStream_t s, size_t ti, void* S) {
   hipError_t e;
   const ace_plan* p = c.p;
   const acex::GridArgs& g = c.g;
-  const int B = p->block;
   const Tile& t = c.bt->tiles[ti];
-  // a full block x block tile with every pair kept (masked builds too)
-  const bool full = t.bi == B && t.bj == B && t.complete;
-  const bool three = c.three_ok && full;           // plane-fitting grids
-  const bool fused = (c.three_ok || c.rows_ok) && full;
+  const bool fused = tile_fused(c, ti);
+  const bool three = (c.three_ok && fused) || tile_list(c, ti);
   const int chunk = p->chunk > 0 ? p->chunk : t.npack;
   for (int c0 = 0; c0 < t.npack; c0 += chunk) {
     const int cnt = std::min(chunk, t.npack - c0);
@@ -631,13 +683,6 @@ int tile_transforms(const BuildCtx& c, hipStream_t s, size_t ti, void* S) {
   return ACE_OK;
 }
 
-// Does tile ti take the fused inverse-z/W pass?
-bool tile_fused(const BuildCtx& c, size_t ti) {
-  const Tile& t = c.bt->tiles[ti];
-  const int B = c.p->block;
-  return (c.three_ok || c.rows_ok) && t.bi == B && t.bj == B && t.complete;
-}
-
 // A5 for tile ti (and, with S2, a second fused tile tj of the same kind and
 // no block in common, in the same launch): the W update from the
 // transforms in scratch.
@@ -654,6 +699,9 @@ int tile_accumulate(const BuildCtx& c, hipStream_t s, size_t ti, const void* S, 
   if (tile_fused(c, ti)) {
     e = acex::launch_zinv_acc(g, B, t.diag, S, c.phi_bulk, W, t_orbs, p->alpha, s, S2,
                               S2 ? c.d_orbs + tj * (size_t)2 * B : nullptr);
+  } else if (tile_list(c, ti)) {
+    e = acex::launch_zinv_list(g, B, t.diag, S, c.phi_bulk, W, t_orbs,
+                               c.d_groups + t.group0, t.ngroup, t.useI, t.useJ, p->alpha, s);
   } else {
     e = acex::launch_accumulate(p->prec, B, t.diag, S, c.phi_bulk, W,
                                 full ? nullptr : c.d_meta + t.pack0, t.npack, t_orbs, t.useI,

@@ -50,6 +50,9 @@ hipError_t launch_fwd_yz(const GridArgs& g, const void* phi, const Pack* packs, 
 // transforms, S + 0 .. npack-1 in the canonical row order, folded into W of
 // the tile's orbitals orbs[0..2 block)).
 bool three_pass_ok(int n, int prec, int block);
+// Does a partial tile (complete: every pair of its orbitals kept) or a tile
+// with pairs masked out take three passes too (launch_zinv_list)?
+bool list_ok(int n, int prec, int block, bool complete);
 // Large-grid schedule for full tiles where a plane does not fit
 // (fused_rows_ok): launch_fwd_yz -> launch_poisson_x -> launch_inv_y (the
 // inverse y lines only) -> launch_zinv_acc (inverse z rows folded into W).
@@ -63,6 +66,37 @@ hipError_t launch_zinv_acc(const GridArgs& g, int block, bool diag, const void* 
                            const void* phi, double* W, const int* orbs, double alpha,
                            hipStream_t s, const void* S2 = nullptr,
                            const int* orbs2 = nullptr);
+// One group of an incomplete tile's transforms: count of them from first (from
+// the tile's first), in up to four whole rows; row q is orbital row(q), meets
+// the orbitals mask(q) (bit b: local position b) and starts at transform
+// start(q) of the group.  Whole words, for scalar loads.
+struct TileGroup {
+  static constexpr int kRows = 4;
+  int first_;
+  unsigned size_;    // count | rows << 8
+  unsigned row_;     // a byte per row
+  unsigned start_;   // a byte per row
+  unsigned mask_[2]; // 16 bits per row
+  __host__ __device__ int first() const { return first_; }
+  __host__ __device__ int count() const { return size_ & 255u; }
+  __host__ __device__ int rows() const { return size_ >> 8; }
+  __host__ __device__ int row(int q) const { return (row_ >> (8 * q)) & 255u; }
+  __host__ __device__ int start(int q) const { return (start_ >> (8 * q)) & 255u; }
+  __host__ __device__ unsigned mask(int q) const { return (mask_[q / 2] >> (16 * (q & 1))) & 0xffffu; }
+  void add(int a, int packs, unsigned mask) {
+    const int q = rows();
+    row_ |= (unsigned)a << (8 * q);
+    start_ |= (unsigned)count() << (8 * q);
+    mask_[q / 2] |= mask << (16 * (q & 1));
+    size_ += (unsigned)packs + 256u;
+  }
+};
+// launch_zinv_acc for a tile with pairs missing: useI and useJ as for
+// launch_accumulate.
+hipError_t launch_zinv_list(const GridArgs& g, int block, bool diag, const void* S,
+                            const void* phi, double* W, const int* orbs,
+                            const TileGroup* groups, int ngroups, unsigned useI, unsigned useJ,
+                            double alpha, hipStream_t s);
 // x transforms with the Coulomb multiply between forward and inverse, in place.
 hipError_t launch_poisson_x(const GridArgs& g, void* S, int npack, hipStream_t s);
 // x forward transform and sum of K |Z|^2 per workgroup into part[npack][parts_per_pack].

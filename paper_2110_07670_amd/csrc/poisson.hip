@@ -734,6 +734,26 @@ constexpr bool zinv_ok() {
   else return !plane_ok<T, N>() && !three && zinv_fits<T, N, B, true>();
 }
 
+// First point (x, y0) of inverse-z workgroup bid.
+template <typename T, int N, bool ROWS>
+__device__ __forceinline__ void zinv_point(int bid, int& x, int& y0) {
+  constexpr int YC = zinv_rows<T, N, ROWS>();
+  // workgroups per 128-byte scratch segment (FP32: two)
+  constexpr int H = YC * int(sizeof(cx<T>)) < 128 ? 128 / (YC * int(sizeof(cx<T>))) : 1;
+  if constexpr (!ROWS && H > 1 && N % (H * YC) == 0) {
+    // the H workgroups sharing a segment run back to back on one XCD
+    // (workgroup b runs on XCD b mod 8), so the later ones find the lines in
+    // L2; only where whole segments tile the y rows (else the plain order)
+    const int g = bid >> 3, xcd = bid & 7;
+    const int seg = (g / H) * 8 + xcd;
+    y0 = (seg % (N / (H * YC))) * (H * YC) + (g % H) * YC;
+    x = seg / (N / (H * YC));
+  } else {
+    y0 = (bid % (N / YC)) * YC;
+    x = bid / (N / YC);
+  }
+}
+
 // A workgroup owns the points (x, y0 .. y0 + YC - 1, all z) of a full B x B tile and
 // walks its rows a: the transforms of row a (pairs (a, b0) and (a, b0 + 1))
 // are inverse-transformed along z in LDS; then each thread, one point, folds
@@ -761,20 +781,7 @@ __device__ __forceinline__ void zinv_item(const cx<T>* __restrict__ S,
   const int tid = LOOP ? opaque_tid<NT>() : (int)threadIdx.x;
   const bool act = NT == ACT || tid < ACT;
   int x, y0;
-  // workgroups per 128-byte scratch segment (FP32: two)
-  constexpr int H = YC * int(sizeof(cx<T>)) < 128 ? 128 / (YC * int(sizeof(cx<T>))) : 1;
-  if constexpr (!ROWS && H > 1 && N % (H * YC) == 0) {
-    // the H workgroups sharing a segment run back to back on one XCD
-    // (workgroup b runs on XCD b mod 8), so the later ones find the lines in
-    // L2; only where whole segments tile the y rows (else the plain order)
-    const int g = bid >> 3, xcd = bid & 7;
-    const int seg = (g / H) * 8 + xcd;
-    y0 = (seg % (N / (H * YC))) * (H * YC) + (g % H) * YC;
-    x = seg / (N / (H * YC));
-  } else {
-    y0 = (bid % (N / YC)) * YC;
-    x = bid / (N / YC);
-  }
+  zinv_point<T, N, ROWS>(bid, x, y0);
   for (int i = tid; i < N; i += NT) stw[i] = tw[(i % N2) * (i / N2)];  // stw[k1 N2 + t2] = w^(t2 k1)
   // this thread's point for the W update (consecutive threads: consecutive
   // z); a thread without one reads point (x, y0, z) and writes nothing
@@ -954,6 +961,138 @@ __device__ __forceinline__ void zinv_item(const cx<T>* __restrict__ S,
       __builtin_nontemporal_store(wold[b] - alpha * acc[b],
                                   &W[(int64_t)orbs[(DIAG ? 0 : B) + b] * npts + r]);
   }
+}
+
+// The same pass for a tile with pairs missing (a ragged block at the end of
+// the orbitals, or a mask): its transforms, row-major in a with two pairs of a
+// row each, are taken in groups of up to B / 2
+// whole rows, at most four (TileGroup), so that a group fills the workgroup's
+// z transforms as a row of a full tile does.  The W rows and orbitals of a
+// group's rows are loaded ahead of its transforms; the orbitals that a row
+// meets are a bit mask, walked with scalar branches so that each one's value
+// and sum stay in fixed registers.  The potentials stay out of HBM as on full tiles: the four-pass form wrote them,
+// read them again and took the W update as a pass of its own (48^3 FP64, 32
+// transforms of a 16 x 4 tile: inverse y/z 18 and update 25 us, this pass 30
+// us, and 96^3 FP32 65 + 132 against 201 us, each after a middle pass that
+// costs what the x pass alone did).  list_ok says where it is used.
+template <typename T, int N, int B, bool DIAG>
+__device__ __forceinline__ void zinv_list_item(
+    const cx<T>* __restrict__ S, const cx<T>* __restrict__ tw, const T* __restrict__ phi,
+    double* __restrict__ W, const int* __restrict__ orbs,
+    const TileGroup* __restrict__ groups, int ngroups, unsigned useI, unsigned useJ, double alpha,
+    int64_t npts, int bid, cx<T>* __restrict__ lds, cx<T>* __restrict__ stw) {
+  constexpr int N1 = fft_split<N>::N1, N2 = fft_split<N>::N2, P = N + 1;
+  constexpr int G = B / 2, YC = zinv_rows<T, N>(), R = TileGroup::kRows, NT = zinv_threads<T, N>();
+  const int tid = threadIdx.x;
+  int x, y0;
+  zinv_point<T, N, false>(bid, x, y0);
+  for (int i = tid; i < N; i += NT) stw[i] = tw[(i % N2) * (i / N2)];
+  const int c = tid / N, z = tid % N;
+  const int64_t r = ((int64_t)x * N + y0 + c) * N + z;
+  const cx<T>* __restrict__ sx = S + (int64_t)x * N + y0;
+  const unsigned use = DIAG ? useI : useJ;
+  const int* side = DIAG ? orbs : orbs + B;
+  T ph[B];
+  double acc[B];
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+    ph[b] = ((use >> b) & 1u) ? phi[(int64_t)side[b] * npts + r] : T(0);
+    acc[b] = 0.0;
+  }
+  __syncthreads();
+  for (int gi = 0; gi < ngroups; ++gi) {
+    const TileGroup gr = groups[gi];
+    const int rows = gr.rows(), count = gr.count();
+    T phA[R];
+    double wA[R];
+    auto load_rows = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int q = 0; q < R; ++q) {
+        phA[q] = T(0);
+        wA[q] = 0.0;
+        if (q < rows) {
+          const int64_t oa = (int64_t)orbs[gr.row(q)] * npts + r;
+          phA[q] = phi[oa];
+          if constexpr (!DIAG) wA[q] = __builtin_nontemporal_load(&W[oa]);
+        }
+      }
+    };
+    // FP64 transforms, and 1024 threads, leave no registers for these beside them
+    constexpr bool AHEAD = sizeof(T) == 4 && NT <= 960;
+    if constexpr (AHEAD) load_rows();
+    for (int task = tid; task < YC * N1 * count; task += NT) {
+      const int cc = task % YC, k1 = (task / YC) % N1, m = task / (YC * N1);
+      const cx<T>* __restrict__ src = sx + (int64_t)(gr.first() + m) * npts + cc;
+      cx<T> v[N2];
+#pragma unroll
+      for (int t = 0; t < N2; ++t) v[t] = ld_stream(&src[(int64_t)(t + N2 * k1) * N * N]);
+      dft<N2, true>(v);
+#pragma unroll
+      for (int t = 0; t < N2; ++t) lds[(m * YC + cc) * P + t + N2 * k1] = v[t];
+    }
+    lds_barrier();
+    for (int task = tid; task < YC * N2 * count; task += NT) {
+      const int t2 = task % N2;
+      const int cc = (task / N2) % YC, m = task / (N2 * YC);
+      cx<T> v[N1];
+#pragma unroll
+      for (int k1 = 0; k1 < N1; ++k1)
+        v[k1] = cmulc(lds[(m * YC + cc) * P + t2 + N2 * k1], stw[k1 * N2 + t2]);
+      dft<N1, true>(v);
+#pragma unroll
+      for (int j1 = 0; j1 < N1; ++j1) lds[(m * YC + cc) * P + t2 + N2 * j1] = v[j1];
+    }
+    if constexpr (!AHEAD) load_rows();
+    lds_barrier();
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      if (q >= rows) break;
+      const int a = gr.row(q);
+      const unsigned mask = gr.mask(q);
+      const double pA = double(phA[q]);
+      double accA = 0.0;
+      // the row's pairs in order: value i is half i & 1 of transform i / 2
+      int i = 2 * gr.start(q);
+      const T* val = reinterpret_cast<const T*>(lds + c * P + z);
+      sfor<0, B>([&](auto bc) __attribute__((always_inline)) {
+        constexpr int b = decltype(bc)::value;
+        if ((mask >> b) & 1u) {
+          const double v = double(val[(i >> 1) * (2 * YC * P) + (i & 1)]);
+          ++i;
+          accA += v * double(ph[b]);
+          acc[b] += v * (DIAG && b == a ? 0.0 : pA);
+        }
+      });
+      if constexpr (DIAG)
+        sfor<0, B>([&](auto bc) __attribute__((always_inline)) {
+          constexpr int b = decltype(bc)::value;
+          acc[b] += b == a ? accA : 0.0;  // a select: a branch per b becomes an indexed array
+        });
+      else
+        __builtin_nontemporal_store(wA[q] - alpha * accA, &W[(int64_t)orbs[a] * npts + r]);
+    }
+    lds_barrier();
+  }
+  double wold[B];
+#pragma unroll
+  for (int b = 0; b < B; ++b)
+    wold[b] = ((use >> b) & 1u) ? __builtin_nontemporal_load(&W[(int64_t)side[b] * npts + r]) : 0.0;
+#pragma unroll
+  for (int b = 0; b < B; ++b)
+    if ((use >> b) & 1u)
+      __builtin_nontemporal_store(wold[b] - alpha * acc[b], &W[(int64_t)side[b] * npts + r]);
+}
+
+template <typename T, int N, int B, bool DIAG>
+__global__ __launch_bounds__((zinv_threads<T, N>())) void k_zinv_list(
+    const cx<T>* __restrict__ S, const cx<T>* __restrict__ tw, const T* __restrict__ phi,
+    double* __restrict__ W, const int* __restrict__ orbs,
+    const TileGroup* __restrict__ groups, int ngroups, unsigned useI, unsigned useJ, double alpha,
+    int64_t npts) {
+  __shared__ cx<T> lds[(B / 2) * zinv_rows<T, N>() * (N + 1)];
+  __shared__ cx<T> stw[N];
+  zinv_list_item<T, N, B, DIAG>(S, tw, phi, W, orbs, groups, ngroups, useI, useJ, alpha, npts,
+                                blockIdx.x, lds, stw);
 }
 
 // One launch may serve two tiles with disjoint orbital blocks (their W rows
@@ -2273,6 +2412,27 @@ static hipError_t zinv_t(const GridArgs& g, bool diag, const void* S, const void
     return zinv_launch<T, N, B, true>(g, diag, S, phi, W, orbs, alpha, s, S2, orbs2);
 }
 
+template <typename T, int N, int B>
+static hipError_t zinv_list_t(const GridArgs& g, bool diag, const void* S, const void* phi,
+                              double* W, const int* orbs, const TileGroup* groups, int ngroups,
+                              unsigned useI, unsigned useJ, double alpha, hipStream_t s) {
+  if constexpr (zinv_ok<T, N, B>()) {
+    const dim3 grid(N * (N / zinv_rows<T, N>())), block(zinv_threads<T, N>());
+    if (diag)
+      hipLaunchKernelGGL((k_zinv_list<T, N, B, true>), grid, block, 0, s,
+                         static_cast<const cx<T>*>(S), static_cast<const cx<T>*>(g.tw),
+                         static_cast<const T*>(phi), W, orbs, groups, ngroups, useI, useJ, alpha,
+                         g.npts);
+    else
+      hipLaunchKernelGGL((k_zinv_list<T, N, B, false>), grid, block, 0, s,
+                         static_cast<const cx<T>*>(S), static_cast<const cx<T>*>(g.tw),
+                         static_cast<const T*>(phi), W, orbs, groups, ngroups, useI, useJ, alpha,
+                         g.npts);
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
+}
+
 // the large-grid schedule's inverse y lines (its inverse z is fused with W)
 template <typename T, int N>
 static hipError_t inv_y_t(const GridArgs& g, void* S, int npack, hipStream_t s) {
@@ -2357,6 +2517,22 @@ bool three_pass_ok(int n, int prec, int block) {
   }
 }
 
+// The fused pass of incomplete tiles against the four-pass form (build + apply
+// or screened build; ms):
+//   FP64, up to 120^3: ragged 64^3 x 23 orbitals 1.23 -> 0.78, 80^3 x 75 15.3
+//     -> 14.0, 120^3 x 100 101.1 -> 96.5; screened 96^3 x 128 22.0 -> 18.5,
+//     120^3 x 128 37.6 -> 29.5.  At 128^3 its 1024 threads spill: screened
+//     x 100 35.4 -> 42.4.
+//   FP32, ragged: 40^3 x 9 0.197 -> 0.089, 128^3 x 57 23.6 -> 21.9; screened
+//     96^3 x 160 21.5 -> 20.9, 80^3 x 140 11.7 -> 12.0, 128^3 x 200 49.7 ->
+//     50.1: the W rows of a sparse tile outweigh its FP32 transforms.  At
+//     120^3 and below 40^3 the two forms contract different multiply-adds,
+//     and there FP32 tiles keep the four-pass form's values.
+bool list_ok(int n, int prec, int block, bool complete) {
+  if (!three_pass_ok(n, prec, block)) return false;
+  return prec == 0 ? n <= 120 : complete && n >= 40 && n != 120;
+}
+
 bool fused_rows_ok(int n, int prec, int block) {
   switch (n) {
 #define X(N)                                                                                \
@@ -2409,6 +2585,25 @@ hipError_t launch_zinv_acc(const GridArgs& g, int block, bool diag, const void* 
     return hipErrorInvalidValue;
     ACEX_SIZES(X)
 #undef X
+    default: return hipErrorInvalidValue;
+  }
+}
+
+hipError_t launch_zinv_list(const GridArgs& g, int block, bool diag, const void* S,
+                            const void* phi, double* W, const int* orbs,
+                            const TileGroup* groups, int ngroups, unsigned useI, unsigned useJ,
+                            double alpha, hipStream_t s) {
+  switch (g.n) {
+#define Y(T, N, B) \
+  zinv_list_t<T, N, B>(g, diag, S, phi, W, orbs, groups, ngroups, useI, useJ, alpha, s)
+#define X(N)                                                              \
+  case N:                                                                 \
+    if (block == 16) return g.prec == 0 ? Y(double, N, 16) : Y(float, N, 16); \
+    if (block == 8) return g.prec == 0 ? Y(double, N, 8) : Y(float, N, 8);    \
+    return hipErrorInvalidValue;
+    ACEX_SIZES(X)
+#undef X
+#undef Y
     default: return hipErrorInvalidValue;
   }
 }
