@@ -55,6 +55,8 @@ struct Tile {
   int pack0, npack;
   unsigned useI, useJ;  // local orbitals with at least one kept pair
   bool complete;        // every pair of the tile kept: canonical pack order
+  int orb0, rows;       // its orbital list: rows entries (I), then block entries (J)
+  bool merge;           // not a full complete tile: tiles of one column block merge
   int group0, ngroup;   // its transforms in groups of rows (incomplete or partial tiles)
 };
 
@@ -293,8 +295,13 @@ std::vector<int> pair_order(int k, int B, const uint8_t* mask) {
 // and (a, d) with d the next kept column of row a; a row's odd leftover is a
 // single-pair transform.  meta receives, per transform, the local positions
 // of its pairs (a0 | b0 << 8 | a1 << 16 | b1 << 24, a1 = 255 for a single
-// pair); orbs receives, per kept tile, its 2B orbital indices (I list, then
-// J list; -1 past a partial block).
+// pair); orbs receives, per kept tile, its orbital indices (I list, then J
+// list, a block each; -1 past a partial block).  Off-diagonal tiles with pairs
+// missing that share their column block become one tile with several I
+// blocks, as many as the scratch holds: fewer, larger launches, and the column
+// block's orbitals and W rows are read and written once for all of them
+// (128 orbitals at 96^3 FP64 screened: MERGEOLD -> MERGENEW ms; 256 at 144^3
+// FP32: MERGEOLD2 -> MERGENEW2).
 // Block pairs (I, J), I <= J, in build order.  FP64 bulk: row by row, so
 // that consecutive tiles share their first block's orbital rows in the
 // last-level cache.  FP32 bulk: diagonal tiles, then the others, each kind
@@ -375,64 +382,95 @@ void build_schedule(const ace_plan* p, const uint8_t* mask, std::vector<Pack>& p
   meta.clear();
   orbs.clear();
   groups.clear();
+  auto on = [&](int i, int j) { return mask_on(mask, k, std::min(i, j), std::max(i, j)); };
+  // full tiles with every pair kept in tile_order's order, then the others by
+  // column block, so that those of one block can be merged
+  std::vector<std::pair<int, int>> full, rest;
   for (const auto& IJ : tile_order(nb, k % B == 0, p->prec == ACE_FP32)) {
-    {
-      const int I = IJ.first, J = IJ.second;
-      Tile t;
-      t.i0 = I * B;
-      t.j0 = J * B;
-      t.bi = std::min(B, k - t.i0);
-      t.bj = std::min(B, k - t.j0);
-      t.diag = (I == J);
-      t.pack0 = (int)packs.size();
-      t.useI = t.useJ = 0u;
-      int local = 0, kept = 0;
-      for (int a = 0; a < t.bi; ++a) {
-        int half = 0;
-        Pack cur{-1, -1, -1, -1};
-        int code = 0;
-        for (int b = t.diag ? a : 0; b < t.bj; ++b) {
-          const int i = ord[t.i0 + a], j = ord[t.j0 + b];
-          if (!mask_on(mask, k, std::min(i, j), std::max(i, j))) continue;
-          ++kept;
-          t.useI |= 1u << a;
-          if (t.diag) t.useI |= 1u << b;
-          else t.useJ |= 1u << b;
-          if (half == 0) {
-            cur = Pack{i, j, -1, -1};
-            code = a | (b << 8);
-            half = 1;
-          } else {
-            cur.e = acex::kPackUnit;
-            cur.d = j;
-            packs.push_back(cur);
-            meta.push_back(code | (a << 16) | (b << 24));
-            ++local;
-            half = 0;
-          }
+    const int i0 = IJ.first * B, j0 = IJ.second * B;
+    bool whole = i0 + B <= k && j0 + B <= k;
+    for (int a = 0; whole && a < B; ++a)
+      for (int b = IJ.first == IJ.second ? a : 0; whole && b < B; ++b)
+        whole = on(ord[i0 + a], ord[j0 + b]);
+    (whole ? full : rest).push_back(IJ);
+  }
+  std::stable_sort(rest.begin(), rest.end(),
+                   [](const std::pair<int, int>& x, const std::pair<int, int>& y) {
+                     return x.second < y.second;
+                   });
+  const size_t nfull = full.size();
+  full.insert(full.end(), rest.begin(), rest.end());
+  // transforms that the scratch holds, and rows that a byte of meta names
+  const int max_packs = (int)((p->off_part - p->off_S) / p->s_buf_bytes) * p->max_pack_tile;
+  const int max_rows = 240;
+  std::vector<int> side;  // the J list of the tile being built, written when it is closed
+  auto close = [&]() {
+    if (tiles.empty() || side.empty()) return;
+    Tile& t = tiles.back();
+    orbs.insert(orbs.end(), side.begin(), side.end());
+    side.clear();
+    t.group0 = (int)groups.size();
+    if (!(t.complete && t.bi == B && t.bj == B))
+      row_groups(meta.data() + t.pack0, t.npack, B, groups);
+    t.ngroup = (int)groups.size() - t.group0;
+  };
+  for (size_t q = 0; q < full.size(); ++q) {
+    const int I = full[q].first, J = full[q].second;
+    Tile t;
+    t.i0 = I * B;
+    t.j0 = J * B;
+    t.bi = std::min(B, k - t.i0);
+    t.bj = std::min(B, k - t.j0);
+    t.diag = (I == J);
+    t.pack0 = (int)packs.size();
+    t.useI = t.useJ = 0u;
+    int kept = 0;
+    for (int a = 0; a < t.bi; ++a) {
+      bool open = false;
+      for (int b = t.diag ? a : 0; b < t.bj; ++b) {
+        const int i = ord[t.i0 + a], j = ord[t.j0 + b];
+        if (!on(i, j)) continue;
+        ++kept;
+        t.useI |= 1u << a;
+        if (t.diag) t.useI |= 1u << b;
+        else t.useJ |= 1u << b;
+        if (!open) {
+          packs.push_back(Pack{i, j, -1, -1});
+          meta.push_back(a | (b << 8) | (255 << 16));
+        } else {
+          packs.back().e = acex::kPackUnit;
+          packs.back().d = j;
+          meta.back() = (meta.back() & 0xffff) | (a << 16) | (b << 24);
         }
-        if (half == 1) {
-          packs.push_back(cur);
-          meta.push_back(code | (255 << 16));
-          ++local;
-        }
-      }
-      t.npack = local;
-      t.complete = kept == (t.diag ? t.bi * (t.bi + 1) / 2 : t.bi * t.bj);
-      t.group0 = (int)groups.size();
-      if (!(t.complete && t.bi == B && t.bj == B))
-        row_groups(meta.data() + t.pack0, local, B, groups);
-      t.ngroup = (int)groups.size() - t.group0;
-      if (t.npack > 0) {
-        tiles.push_back(t);
-        for (int a = 0; a < B; ++a) orbs.push_back(a < t.bi ? ord[t.i0 + a] : -1);
-        for (int b = 0; b < B; ++b) orbs.push_back(b < t.bj ? ord[t.j0 + b] : -1);
-      } else {
-        packs.resize(t.pack0);
-        meta.resize(t.pack0);
+        open = !open;
       }
     }
+    t.npack = (int)packs.size() - t.pack0;
+    t.complete = kept == (t.diag ? t.bi * (t.bi + 1) / 2 : t.bi * t.bj);
+    if (t.npack == 0) continue;
+    Tile* last = tiles.empty() || side.empty() ? nullptr : &tiles.back();
+    if (q >= nfull && last && !t.diag && !last->diag && last->j0 == t.j0 && last->merge &&
+        last->npack + t.npack <= max_packs && last->rows + B <= max_rows) {
+      for (int m = t.pack0; m < t.pack0 + t.npack; ++m) {
+        const int a1 = (meta[m] >> 16) & 255, row = (meta[m] & 255) + last->rows;
+        meta[m] = (meta[m] & 0xff00ff00) | row | (a1 == 255 ? 255 << 16 : row << 16);
+      }
+      last->npack += t.npack;
+      last->useJ |= t.useJ;
+      last->bi += t.bi;
+      last->complete = last->complete && t.complete;
+      last->rows += B;
+    } else {
+      close();
+      t.orb0 = (int)orbs.size();
+      t.rows = B;
+      t.merge = q >= nfull;
+      tiles.push_back(t);
+      for (int b = 0; b < B; ++b) side.push_back(b < t.bj ? ord[t.j0 + b] : -1);
+    }
+    for (int a = 0; a < B; ++a) orbs.push_back(a < t.bi ? ord[t.i0 + a] : -1);
   }
+  close();
 }
 
 // Energy schedule: the pairs tile by tile as in a build, so that a launch reads
@@ -694,18 +732,18 @@ int tile_accumulate(const BuildCtx& c, hipStream_t s, size_t ti, const void* S, 
   const int B = p->block;
   const Tile& t = c.bt->tiles[ti];
   const bool full = t.bi == B && t.bj == B && t.complete;
-  const int* t_orbs = c.d_orbs + ti * (size_t)2 * B;
+  const int* t_orbs = c.d_orbs + t.orb0;
   ProfScope ps(p, 3, s);
   if (tile_fused(c, ti)) {
     e = acex::launch_zinv_acc(g, B, t.diag, S, c.phi_bulk, W, t_orbs, p->alpha, s, S2,
-                              S2 ? c.d_orbs + tj * (size_t)2 * B : nullptr);
+                              S2 ? c.d_orbs + c.bt->tiles[tj].orb0 : nullptr);
   } else if (tile_list(c, ti)) {
-    e = acex::launch_zinv_list(g, B, t.diag, S, c.phi_bulk, W, t_orbs,
+    e = acex::launch_zinv_list(g, B, t.diag, S, c.phi_bulk, W, t_orbs, t_orbs + t.rows,
                                c.d_groups + t.group0, t.ngroup, t.useI, t.useJ, p->alpha, s);
   } else {
     e = acex::launch_accumulate(p->prec, B, t.diag, S, c.phi_bulk, W,
-                                full ? nullptr : c.d_meta + t.pack0, t.npack, t_orbs, t.useI,
-                                t.useJ, p->alpha, p->npts, s);
+                                full ? nullptr : c.d_meta + t.pack0, t.npack, t_orbs,
+                                t_orbs + t.rows, t.useI, t.useJ, p->alpha, p->npts, s);
   }
   return e == hipSuccess ? ACE_OK : hip_fail(e);
 }
@@ -1510,7 +1548,7 @@ int ace_batch_build(ace_batch* b, void* stream, void* ws, size_t ws_bytes,
         sg.S = pw + p->off_S;
         sg.tw = pw + p->off_tab + bt.o_tw;
         sg.W = W[k];
-        sg.orbs = reinterpret_cast<const int*>(pw + p->off_tab + bt.o_orbs) + (size_t)ti * 2 * p->block;
+        sg.orbs = reinterpret_cast<const int*>(pw + p->off_tab + bt.o_orbs) + bt.tiles[ti].orb0;
         b->seg_pinned[i] = sg;
       }
       b->seg_key = std::move(sk);

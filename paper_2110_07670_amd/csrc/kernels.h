@@ -94,7 +94,7 @@ struct TileGroup {
 // launch_zinv_acc for a tile with pairs missing: useI and useJ as for
 // launch_accumulate.
 hipError_t launch_zinv_list(const GridArgs& g, int block, bool diag, const void* S,
-                            const void* phi, double* W, const int* orbs,
+                            const void* phi, double* W, const int* orbs, const int* jorbs,
                             const TileGroup* groups, int ngroups, unsigned useI, unsigned useJ,
                             double alpha, hipStream_t s);
 // x transforms with the Coulomb multiply between forward and inverse, in place.
@@ -126,12 +126,13 @@ hipError_t launch_inv_yz(const GridArgs& g, void* S, int npack, hipStream_t s);
 // meta[p] = a0 | b0 << 8 | a1 << 16 | b1 << 24: local positions of the pairs
 // in the real / imaginary half of transform p (a1 = 255: single pair);
 // meta == nullptr: a full unmasked B x B tile in the canonical a-major order.
-// orbs: the tile's 2B orbital indices (I list, then J list); useI / useJ:
-// local orbitals with at least one pair.
+// orbs, jorbs: the tile's orbital indices, I list (several blocks for a merged
+// off-diagonal tile) and J list (full tiles: right after the I list's block);
+// useI / useJ: local orbitals with at least one pair (diagonal / off it).
 // phi: the orbitals in the bulk precision (FP64, or the FP32 copy).
 hipError_t launch_accumulate(int prec, int block, bool diag, const void* S, const void* phi,
                              double* W, const int* meta, int npack, const int* orbs,
-                             unsigned useI, unsigned useJ, double alpha, int64_t npts,
+                             const int* jorbs, unsigned useI, unsigned useJ, double alpha, int64_t npts,
                              hipStream_t s);
 
 // ---- Batches: one persistent launch per pass over the three-pass tiles of

@@ -979,7 +979,7 @@ template <typename T, int N, int B, bool DIAG>
 __device__ __forceinline__ void zinv_list_item(
     const cx<T>* __restrict__ S, const cx<T>* __restrict__ tw, const T* __restrict__ phi,
     double* __restrict__ W, const int* __restrict__ orbs,
-    const TileGroup* __restrict__ groups, int ngroups, unsigned useI, unsigned useJ, double alpha,
+    const int* __restrict__ jorbs, const TileGroup* __restrict__ groups, int ngroups, unsigned useI, unsigned useJ, double alpha,
     int64_t npts, int bid, cx<T>* __restrict__ lds, cx<T>* __restrict__ stw) {
   constexpr int N1 = fft_split<N>::N1, N2 = fft_split<N>::N2, P = N + 1;
   constexpr int G = B / 2, YC = zinv_rows<T, N>(), R = TileGroup::kRows, NT = zinv_threads<T, N>();
@@ -991,7 +991,7 @@ __device__ __forceinline__ void zinv_list_item(
   const int64_t r = ((int64_t)x * N + y0 + c) * N + z;
   const cx<T>* __restrict__ sx = S + (int64_t)x * N + y0;
   const unsigned use = DIAG ? useI : useJ;
-  const int* side = DIAG ? orbs : orbs + B;
+  const int* __restrict__ side = DIAG ? orbs : jorbs;
   T ph[B];
   double acc[B];
 #pragma unroll
@@ -1087,11 +1087,11 @@ template <typename T, int N, int B, bool DIAG>
 __global__ __launch_bounds__((zinv_threads<T, N>())) void k_zinv_list(
     const cx<T>* __restrict__ S, const cx<T>* __restrict__ tw, const T* __restrict__ phi,
     double* __restrict__ W, const int* __restrict__ orbs,
-    const TileGroup* __restrict__ groups, int ngroups, unsigned useI, unsigned useJ, double alpha,
+    const int* __restrict__ jorbs, const TileGroup* __restrict__ groups, int ngroups, unsigned useI, unsigned useJ, double alpha,
     int64_t npts) {
   __shared__ cx<T> lds[(B / 2) * zinv_rows<T, N>() * (N + 1)];
   __shared__ cx<T> stw[N];
-  zinv_list_item<T, N, B, DIAG>(S, tw, phi, W, orbs, groups, ngroups, useI, useJ, alpha, npts,
+  zinv_list_item<T, N, B, DIAG>(S, tw, phi, W, orbs, jorbs, groups, ngroups, useI, useJ, alpha, npts,
                                 blockIdx.x, lds, stw);
 }
 
@@ -1782,7 +1782,8 @@ __global__ __launch_bounds__(256) void k_pair_scale(Pack* __restrict__ packs,
 // (no atomics), so W is bitwise reproducible.  orbs: the tile's orbitals,
 // I list (B entries) then J list (B entries).
 //
-// General (masked) tiles: meta[p] = a0 | b0 << 8 | a1 << 16 | b1 << 24 gives
+// General (masked) tiles, several I blocks of one column block among them (jorbs:
+// the J list): meta[p] = a0 | b0 << 8 | a1 << 16 | b1 << 24 gives
 // the local positions of transform p's pair in the real (a0, b0) and
 // imaginary (a1, b1; a1 = 255 when absent) half; useI / useJ flag the
 // orbitals with at least one pair.  Transforms come row-major in a (both
@@ -1805,8 +1806,8 @@ __device__ __forceinline__ void w_sub(double* p, double d) {
 template <typename TS, int B, bool DIAG>
 __global__ __launch_bounds__(kAccThreads) void k_accumulate(
     const cx<TS>* __restrict__ S, const TS* __restrict__ phi, double* __restrict__ W,
-    const int* __restrict__ meta, int npack, const int* __restrict__ orbs, unsigned useI,
-    unsigned useJ, double alpha, int64_t npts) {
+    const int* __restrict__ meta, int npack, const int* __restrict__ orbs,
+    const int* __restrict__ jorbs, unsigned useI, unsigned useJ, double alpha, int64_t npts) {
   __shared__ TS sph[B][kAccThreads];
   __shared__ double sacc[B][kAccThreads];
   const int t = threadIdx.x;
@@ -1814,7 +1815,7 @@ __global__ __launch_bounds__(kAccThreads) void k_accumulate(
   if (r >= npts) return;  // no barriers below
   // the other side: the J list off the diagonal, the tile's one list on it
   const unsigned use = DIAG ? useI : useJ;
-  const int* side = DIAG ? orbs : orbs + B;
+  const int* __restrict__ side = DIAG ? orbs : jorbs;
 #pragma unroll
   for (int b = 0; b < B; ++b) {
     sph[b][t] = ((use >> b) & 1u) ? phi[(int64_t)side[b] * npts + r] : TS(0);
@@ -2414,19 +2415,20 @@ static hipError_t zinv_t(const GridArgs& g, bool diag, const void* S, const void
 
 template <typename T, int N, int B>
 static hipError_t zinv_list_t(const GridArgs& g, bool diag, const void* S, const void* phi,
-                              double* W, const int* orbs, const TileGroup* groups, int ngroups,
+                              double* W, const int* orbs, const int* jorbs,
+                              const TileGroup* groups, int ngroups,
                               unsigned useI, unsigned useJ, double alpha, hipStream_t s) {
   if constexpr (zinv_ok<T, N, B>()) {
     const dim3 grid(N * (N / zinv_rows<T, N>())), block(zinv_threads<T, N>());
     if (diag)
       hipLaunchKernelGGL((k_zinv_list<T, N, B, true>), grid, block, 0, s,
                          static_cast<const cx<T>*>(S), static_cast<const cx<T>*>(g.tw),
-                         static_cast<const T*>(phi), W, orbs, groups, ngroups, useI, useJ, alpha,
+                         static_cast<const T*>(phi), W, orbs, jorbs, groups, ngroups, useI, useJ, alpha,
                          g.npts);
     else
       hipLaunchKernelGGL((k_zinv_list<T, N, B, false>), grid, block, 0, s,
                          static_cast<const cx<T>*>(S), static_cast<const cx<T>*>(g.tw),
-                         static_cast<const T*>(phi), W, orbs, groups, ngroups, useI, useJ, alpha,
+                         static_cast<const T*>(phi), W, orbs, jorbs, groups, ngroups, useI, useJ, alpha,
                          g.npts);
     return hipGetLastError();
   }
@@ -2590,12 +2592,12 @@ hipError_t launch_zinv_acc(const GridArgs& g, int block, bool diag, const void* 
 }
 
 hipError_t launch_zinv_list(const GridArgs& g, int block, bool diag, const void* S,
-                            const void* phi, double* W, const int* orbs,
+                            const void* phi, double* W, const int* orbs, const int* jorbs,
                             const TileGroup* groups, int ngroups, unsigned useI, unsigned useJ,
                             double alpha, hipStream_t s) {
   switch (g.n) {
 #define Y(T, N, B) \
-  zinv_list_t<T, N, B>(g, diag, S, phi, W, orbs, groups, ngroups, useI, useJ, alpha, s)
+  zinv_list_t<T, N, B>(g, diag, S, phi, W, orbs, jorbs, groups, ngroups, useI, useJ, alpha, s)
 #define X(N)                                                              \
   case N:                                                                 \
     if (block == 16) return g.prec == 0 ? Y(double, N, 16) : Y(float, N, 16); \
@@ -2709,8 +2711,8 @@ hipError_t launch_pair_scale(Pack* packs, int* codes, int npack, const double* o
 
 template <typename TS, int B>
 static hipError_t acc_t(bool diag, const void* S, const void* phi_v, double* W, const int* meta,
-                        int npack, const int* orbs, unsigned useI, unsigned useJ, double alpha,
-                        int64_t npts, hipStream_t s) {
+                        int npack, const int* orbs, const int* jorbs, unsigned useI,
+                        unsigned useJ, double alpha, int64_t npts, hipStream_t s) {
   const TS* phi = static_cast<const TS*>(phi_v);
   if (meta == nullptr) {
     const dim3 grid((unsigned)((npts + 255) / 256));
@@ -2725,28 +2727,28 @@ static hipError_t acc_t(bool diag, const void* S, const void* phi_v, double* W, 
   const dim3 grid((unsigned)((npts + kAccThreads - 1) / kAccThreads));
   if (diag)
     hipLaunchKernelGGL((k_accumulate<TS, B, true>), grid, dim3(kAccThreads), 0, s,
-                       static_cast<const cx<TS>*>(S), phi, W, meta, npack, orbs, useI, useJ,
+                       static_cast<const cx<TS>*>(S), phi, W, meta, npack, orbs, jorbs, useI, useJ,
                        alpha, npts);
   else
     hipLaunchKernelGGL((k_accumulate<TS, B, false>), grid, dim3(kAccThreads), 0, s,
-                       static_cast<const cx<TS>*>(S), phi, W, meta, npack, orbs, useI, useJ,
+                       static_cast<const cx<TS>*>(S), phi, W, meta, npack, orbs, jorbs, useI, useJ,
                        alpha, npts);
   return hipGetLastError();
 }
 
 hipError_t launch_accumulate(int prec, int block, bool diag, const void* S, const void* phi,
                              double* W, const int* meta, int npack, const int* orbs,
-                             unsigned useI, unsigned useJ, double alpha, int64_t npts,
-                             hipStream_t s) {
+                             const int* jorbs, unsigned useI, unsigned useJ, double alpha,
+                             int64_t npts, hipStream_t s) {
   if (block == 16)
-    return prec == 0 ? acc_t<double, 16>(diag, S, phi, W, meta, npack, orbs, useI, useJ, alpha,
+    return prec == 0 ? acc_t<double, 16>(diag, S, phi, W, meta, npack, orbs, jorbs, useI, useJ, alpha,
                                          npts, s)
-                     : acc_t<float, 16>(diag, S, phi, W, meta, npack, orbs, useI, useJ, alpha,
+                     : acc_t<float, 16>(diag, S, phi, W, meta, npack, orbs, jorbs, useI, useJ, alpha,
                                         npts, s);
   if (block == 8)
-    return prec == 0 ? acc_t<double, 8>(diag, S, phi, W, meta, npack, orbs, useI, useJ, alpha,
+    return prec == 0 ? acc_t<double, 8>(diag, S, phi, W, meta, npack, orbs, jorbs, useI, useJ, alpha,
                                         npts, s)
-                     : acc_t<float, 8>(diag, S, phi, W, meta, npack, orbs, useI, useJ, alpha,
+                     : acc_t<float, 8>(diag, S, phi, W, meta, npack, orbs, jorbs, useI, useJ, alpha,
                                        npts, s);
   return hipErrorInvalidValue;
 }
