@@ -300,8 +300,8 @@ std::vector<int> pair_order(int k, int B, const uint8_t* mask) {
 // missing that share their column block become one tile with several I
 // blocks, as many as the scratch holds: fewer, larger launches, and the column
 // block's orbitals and W rows are read and written once for all of them
-// (128 orbitals at 96^3 FP64 screened: MERGEOLD -> MERGENEW ms; 256 at 144^3
-// FP32: MERGEOLD2 -> MERGENEW2).
+// (128 orbitals at 96^3 FP64 screened: 19.0 -> 18.3 ms; 160 at 96^3 FP32: 20.9 ->
+// 19.4; 256 at 144^3 FP32: 126.5 -> 120.5).
 // Block pairs (I, J), I <= J, in build order.  FP64 bulk: row by row, so
 // that consecutive tiles share their first block's orbital rows in the
 // last-level cache.  FP32 bulk: diagonal tiles, then the others, each kind
@@ -777,24 +777,18 @@ int build_end(const ace_plan* p, hipStream_t s, char* w, const double* phi, doub
                               false, nullptr, s);
     if (e != hipSuccess) return hip_fail(e);
   }
-  // ---- A7: -M = L L^T, L^{-1}
+  // ---- A7, A10: -M = L L^T, L^{-1}; E_x = tr(M)
   double* L = reinterpret_cast<double*>(w + p->off_L);
   double* Linv = reinterpret_cast<double*>(w + p->off_Linv);
   {
     ProfScope ps(p, 5, s);
-    e = acex::launch_cholesky_inv(M, p->n_orb, L, Linv, info, s);
+    e = acex::launch_cholesky_inv(M, p->n_orb, L, Linv, info, ex, s);
     if (e != hipSuccess) return hip_fail(e);
   }
   // ---- A8: xi = W L^{-T}, i.e. xi_k = sum_i Linv[k][i] W_i
   {
     ProfScope ps(p, 6, s);
     e = acex::launch_gemm_ab(Linv, W, p->n_orb, p->n_orb, p->npts, 1.0, xi, true, info, s);
-    if (e != hipSuccess) return hip_fail(e);
-  }
-  // ---- A10: E_x = tr(M)
-  {
-    ProfScope ps(p, 7, s);
-    e = acex::launch_trace(M, p->n_orb, ex, s);
     if (e != hipSuccess) return hip_fail(e);
   }
   return ACE_OK;

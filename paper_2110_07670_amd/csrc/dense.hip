@@ -385,16 +385,21 @@ void abt_launch(bool vec, dim3 grid, hipStream_t s, const double* A, const doubl
 // the reduction of twice the partial sums 10 us more) and four for the
 // smaller ones; at least eight steps per wave; and no more partial sums than
 // the operands themselves are large (each is written and read once more).
-int gemm_abt_splits(int m, int n, int64_t K) {
+static int abt_splits(int m, int n, int64_t K, int64_t tiles) {
   const AbtShape sm = abt_shape(m), sn = abt_shape(n);
-  const int64_t tiles = (int64_t)((m + abt_tile(m) - 1) / abt_tile(m)) *
-                        ((n + abt_tile(n) - 1) / abt_tile(n));
   const int wk = 4 / (sm.w * sn.w);
   const int64_t want = sm.r * sn.r * sm.w * sn.w >= 32 ? 512 : 1024;
   int64_t ns = want / tiles;
   ns = std::min(ns, (K + 64 * wk - 1) / (64 * wk));
   ns = std::min(ns, K * (m + n) / (2 * (int64_t)m * n));
   return (int)std::max<int64_t>(ns, 1);
+}
+
+// The most that a product of these sizes takes: a square one may be symmetric,
+// whose fewer tiles (one triangle) are split further.
+int gemm_abt_splits(int m, int n, int64_t K) {
+  const int64_t tm = (m + abt_tile(m) - 1) / abt_tile(m), tn = (n + abt_tile(n) - 1) / abt_tile(n);
+  return abt_splits(m, n, K, m == n ? tm * (tm + 1) / 2 : tm * tn);
 }
 
 hipError_t launch_gemm_abt(const double* A, const double* B, int m, int n, int64_t K,
@@ -404,15 +409,17 @@ hipError_t launch_gemm_abt(const double* A, const double* B, int m, int n, int64
   const int tiles_m = (m + abt_tile(m) - 1) / abt_tile(m);
   const int tiles_n = (n + abt_tile(n) - 1) / abt_tile(n);
   const int wk = 4 / (sm.w * sn.w);
+  // a product of one operand with itself is symmetric, bit for bit (the same
+  // products in the same order): the tiles above the diagonal are mirrored
+  const bool sym = A == B && m == n && tiles_m > 1;
+  const int tiles = sym ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
+  nsplit = std::min(nsplit, abt_splits(m, n, K, tiles));
   int64_t kchunk = (K + nsplit - 1) / nsplit;
   const int unit = m > 64 && n > 64 ? kAbtKT : 8 * wk;
   kchunk = ((kchunk + unit - 1) / unit) * unit;
   const bool vec = K % 8 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0 &&
                    reinterpret_cast<uintptr_t>(B) % 16 == 0;
-  // a product of one operand with itself is symmetric, bit for bit (the same
-  // products in the same order): the tiles above the diagonal are mirrored
-  const bool sym = A == B && m == n && tiles_m > 1;
-  const dim3 grid(sym ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n, nsplit);
+  const dim3 grid(tiles, nsplit);
 #define ACEX_ABT(RM, WM, RN, WN)                                                              \
   if (sm.r == RM && sm.w == WM && sn.r == RN && sn.w == WN)                                   \
     abt_launch<RM, WM, RN, WN>(vec, grid, s, A, B, m, n, K, kchunk, tiles_n, sym, abs_inputs, \
@@ -628,21 +635,32 @@ hipError_t launch_gemm_ab(const double* A, const double* B, int m, int k, int64_
 //      transposed: lj[k][c] = L[j0 + c][k];
 //   2. every row i >= j0: A[i][j0 + c] -= sum_{k < j0} L[i][k] lj[k][c]
 //      (thread = (row, c), k in increasing order);
-//   3. the diagonal block is factored in LDS, unblocked; a non-positive (or
-//      NaN) pivot stops the factorisation with info = column + 1;
+//   3. the diagonal block is factored by one wave, a row per lane in registers,
+//      the pivot column's values read across lanes (in LDS, with three barriers
+//      per column, it took 1 us per column and most of the factorisation); a
+//      non-positive (or NaN) pivot stops the factorisation with info = column + 1;
 //   4. the rows below it are solved against it, L[i][J] = A[i][J] D^{-T}
 //      (one thread per row, the row in registers).
 // k_tri_inv: one workgroup per block column J of X; forward block
 // substitution down the row blocks I >= J with the block column in LDS:
 //   X[I][J] = D_I^{-1} (delta - sum_{J <= K < I} L[I][K] X[K][J]),
 // the triangular solve by one thread per column with the column in
-// registers.  Both are skipped after a failed factorisation (X undefined).
+// registers.  Both are skipped after a failed factorisation (X undefined).  Up
+// to 32 orbitals k_chol_left inverts its one block itself.
 constexpr int kCholNB = 32;
 constexpr int kCholMaxN = 512;
 
+// v of lane l (uniform)
+__device__ __forceinline__ double lane_of(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
 __global__ __launch_bounds__(1024) void k_chol_left(const double* __restrict__ M, int n,
                                                     double* __restrict__ L,
-                                                    int* __restrict__ info) {
+                                                    int* __restrict__ info,
+                                                    double* __restrict__ trace,
+                                                    double* __restrict__ X) {
   __shared__ double lj[kCholMaxN - kCholNB][kCholNB];
   __shared__ double dblk[kCholNB][kCholNB + 1];
   __shared__ int bad;
@@ -653,6 +671,14 @@ __global__ __launch_bounds__(1024) void k_chol_left(const double* __restrict__ M
     L[e] = (j <= i) ? -M[e] : 0.0;
   }
   if (tid == 0) bad = 0;
+  if (tid < 64) {
+    // tr(M): lane sums, then across the wave, in a fixed order
+    double t = 0.0;
+    for (int i = tid; i < n; i += 64) t += M[(int64_t)i * n + i];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) t += __shfl_xor(t, off, 64);
+    if (tid == 0) *trace = t;
+  }
   __syncthreads();
   for (int j0 = 0; j0 < n; j0 += kCholNB) {
     const int w = min(kCholNB, n - j0);
@@ -679,23 +705,31 @@ __global__ __launch_bounds__(1024) void k_chol_left(const double* __restrict__ M
       dblk[r][cc] = L[(int64_t)(j0 + r) * n + j0 + cc];
     }
     __syncthreads();
-    for (int j = 0; j < w; ++j) {
-      const double d = dblk[j][j];
-      if (!(d > 0.0)) {
-        if (tid == 0) bad = j0 + j + 1;
-        break;
+    if (tid < 64) {
+      const int r = tid;  // lanes past w hold zeros and never show
+      double row[kCholNB];
+#pragma unroll
+      for (int cc = 0; cc < kCholNB; ++cc) row[cc] = r < w && cc < w ? dblk[r][cc] : 0.0;
+      bool ok = true;
+#pragma unroll
+      for (int j = 0; j < kCholNB; ++j) {
+        if (ok && j < w) {
+          const double d = lane_of(row[j], j);
+          if (!(d > 0.0)) {
+            ok = false;
+            if (tid == 0) bad = j0 + j + 1;
+          } else {
+            const double ljj = sqrt(d);
+            row[j] = r == j ? ljj : r > j ? row[j] / ljj : row[j];
+#pragma unroll
+            for (int q = j + 1; q < kCholNB; ++q)
+              if (q < w) row[q] -= row[j] * lane_of(row[j], q);
+          }
+        }
       }
-      const double ljj = sqrt(d);
-      __syncthreads();
-      if (tid == 0) dblk[j][j] = ljj;
-      if (tid > j && tid < w) dblk[tid][j] /= ljj;
-      __syncthreads();
-      const int rem = w - j - 1;
-      for (int e = tid; e < rem * rem; e += 1024) {
-        const int rr = e / rem, kk = e % rem;
-        if (kk <= rr) dblk[j + 1 + rr][j + 1 + kk] -= dblk[j + 1 + rr][j] * dblk[j + 1 + kk][j];
-      }
-      __syncthreads();
+#pragma unroll
+      for (int cc = 0; cc < kCholNB; ++cc)
+        if (r < w && cc < w) dblk[r][cc] = row[cc];
     }
     __syncthreads();
     if (bad) break;
@@ -724,6 +758,20 @@ __global__ __launch_bounds__(1024) void k_chol_left(const double* __restrict__ M
   }
   __syncthreads();
   if (tid == 0) *info = bad;
+  // one block: its inverse right here, a column per thread
+  if (X && !bad && tid < n) {
+    double x[kCholNB];
+#pragma unroll
+    for (int r = 0; r < kCholNB; ++r) {
+      if (r < n) {
+        double v = r == tid ? 1.0 : 0.0;
+#pragma unroll
+        for (int k = 0; k < r; ++k) v -= dblk[r][k] * x[k];
+        x[r] = v / dblk[r][r];
+        X[(int64_t)r * n + tid] = r >= tid ? x[r] : 0.0;
+      }
+    }
+  }
 }
 
 __global__ __launch_bounds__(1024) void k_tri_inv(const double* __restrict__ L, int n,
@@ -779,28 +827,17 @@ __global__ __launch_bounds__(1024) void k_tri_inv(const double* __restrict__ L, 
 }
 
 hipError_t launch_cholesky_inv(const double* M, int n, double* L, double* Linv, int* info,
-                               hipStream_t s) {
+                               double* trace, hipStream_t s) {
   if (n > kCholMaxN || n < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_chol_left, dim3(1), dim3(1024), 0, s, M, n, L, info);
-  hipLaunchKernelGGL(k_tri_inv, dim3((n + kCholNB - 1) / kCholNB), dim3(1024), 0, s, L, n, Linv,
+  hipLaunchKernelGGL(k_chol_left, dim3(1), dim3(1024), 0, s, M, n, L, info, trace,
+                     n <= kCholNB ? Linv : (double*)nullptr);
+  if (n > kCholNB)
+    hipLaunchKernelGGL(k_tri_inv, dim3((n + kCholNB - 1) / kCholNB), dim3(1024), 0, s, L, n, Linv,
                      info);
   return hipGetLastError();
 }
 
 // ------------------------------------------------------------------ reductions
-__global__ void k_trace(const double* __restrict__ M, int n, double* __restrict__ out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double s = 0.0;
-    for (int i = 0; i < n; ++i) s += M[(int64_t)i * n + i];
-    *out = s;
-  }
-}
-
-hipError_t launch_trace(const double* M, int n, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_trace, dim3(1), dim3(64), 0, s, M, n, out);
-  return hipGetLastError();
-}
-
 // Fixed-order weighted sum: 256 contiguous chunks, then the chunk sums in order.
 __global__ __launch_bounds__(256) void k_weighted_sum(const double* __restrict__ e,
                                                       const double* __restrict__ w, int count,

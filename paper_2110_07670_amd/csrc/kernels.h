@@ -193,10 +193,9 @@ hipError_t launch_gemm_ab(const double* A, const double* B, int m, int k, int64_
                           double scale, double* Out, bool tri, const int* skip_if_nonzero,
                           hipStream_t s);
 // -M = L L^T (lower), then Linv = L^{-1}; info = 0 or the order of the first
-// non-positive leading minor.  work: n*n doubles.
+// non-positive leading minor; *trace = tr(M).
 hipError_t launch_cholesky_inv(const double* M, int n, double* L, double* Linv, int* info,
-                               hipStream_t s);
-hipError_t launch_trace(const double* M, int n, double* out, hipStream_t s);
+                               double* trace, hipStream_t s);
 // out = sum_i w[i] e[i] in a fixed order (single workgroup)
 hipError_t launch_weighted_sum(const double* e, const double* w, int count, double* out,
                                hipStream_t s);
