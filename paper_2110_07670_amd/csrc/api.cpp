@@ -170,7 +170,9 @@ void layout(ace_plan* p) {
   p->s_grid_bytes = align256((size_t)p->npts * 2 * bulk);
   p->max_pack_tile = (B * B + 1) / 2;
   p->nsplit = acex::gemm_abt_splits(p->n_orb, p->n_orb, p->npts);
-  p->eparts = std::max(acex::energy_parts_per_pack(p->n), 2 * acex::pair_energy_parts(p->n));
+  p->eparts = p->prec == ACE_FP64
+                  ? std::max(acex::energy_parts_per_pack(p->n), 2 * acex::pair_energy_parts(p->n))
+                  : acex::energy_parts_per_pack(p->n);
   size_t off = 0;
   p->off_tab = off;
   p->tab_bytes = align256((size_t)ntiles * 2 * B * sizeof(int)) +
@@ -473,48 +475,87 @@ void build_schedule(const ace_plan* p, const uint8_t* mask, std::vector<Pack>& p
   close();
 }
 
-// Energy schedule: the pairs tile by tile as in a build, so that a launch reads
-// two blocks of orbitals and not whole rows (96^3 FP64, 128 orbitals: 463
-// against 552 us per 128 transforms); launches are runs of tiles, `first`
-// their first packs.  Two pairs (i, j), (i, j') of one tile row share a
-// transform.  E_x alone (`code` null): off-diagonal pairs share one (both
-// halves carry weight 2), diagonal pairs go alone.  Every pair's energy
-// wanted: the diagonal pair shares one too, and code[2 p], code[2 p + 1] =
-// i n_orb + j of pack p's pairs (-1: none).
+// Energy schedule: two pairs (i, j), (i, j') of one row share a transform.  E_x
+// alone (`code` null): off-diagonal pairs do (both halves carry weight 2),
+// diagonal ones go alone.  Every pair's energy wanted: the diagonal pair
+// shares one too, and code[2 p], code[2 p + 1] = i n_orb + j of pack p's pairs
+// (-1: none).  In FP32 each pair then goes alone (code[p]): the rounding of a
+// shared transform would show in the smaller energy.
+// `first`: the first packs of the launches.  Where there are several and the
+// orbitals far exceed the 256 MB last-level cache (40 at 120^3 FP32, 276 MB, are
+// 2% slower so), the packs go tile by tile as in a
+// build, so that a launch reads two blocks of orbitals and not whole rows
+// (128 orbitals at 96^3 FP64: forward pass 549 us per 128 transforms by rows
+// with the energy pass evicting the orbitals, 427 us per 117 by tiles without).
 void build_energy_schedule(const ace_plan* p, const uint8_t* mask, std::vector<Pack>& packs,
                            std::vector<double>& weight, std::vector<int>* code,
                            std::vector<int>& first) {
-  const int k = p->n_orb, B = p->block, nb = (k + B - 1) / B;
+  const int k = p->n_orb, B = p->block;
+  const bool split = code && p->prec == ACE_FP64;  // two pairs to tell apart
   packs.clear();
   weight.clear();
-  first.assign(1, 0);
-  for (int I = 0; I < nb; ++I)
-    for (int J = I; J < nb; ++J) {
-      const size_t tile0 = packs.size();
-      for (int i = I * B; i < std::min(k, (I + 1) * B); ++i) {
-        bool open = false;
-        for (int j = std::max(i, J * B); j < std::min(k, (J + 1) * B); ++j) {
-          if (!mask_on(mask, k, i, j)) continue;
-          if (open) {
-            packs.back().e = acex::kPackUnit;
-            packs.back().d = j;
-            if (code) code->back() = i * k + j;
-            open = false;
-            continue;
-          }
-          packs.push_back(Pack{i, j, -1, -1});
-          if (code) {
-            code->push_back(i * k + j);
-            code->push_back(-1);
-          } else {
-            weight.push_back((i == j ? -1.0 : -2.0) * p->alpha);
-          }
-          open = code || i != j;
-        }
+  for (int i = 0; i < k; ++i) {
+    bool open = false;
+    for (int j = i; j < k; ++j) {
+      if (!mask_on(mask, k, i, j)) continue;
+      if (open) {
+        packs.back().e = acex::kPackUnit;
+        packs.back().d = j;
+        if (code) code->back() = i * k + j;
+        open = false;
+        continue;
       }
-      if (packs.size() - first.back() > (size_t)p->max_pack_tile) first.push_back((int)tile0);
+      packs.push_back(Pack{i, j, -1, -1});
+      if (code) {
+        code->push_back(i * k + j);
+        if (split) code->push_back(-1);
+      } else {
+        weight.push_back((i == j ? -1.0 : -2.0) * p->alpha);
+      }
+      open = code ? split : i != j;
     }
-  first.push_back((int)packs.size());
+  }
+  first.clear();
+  const size_t np = packs.size(), most = (size_t)p->max_pack_tile;
+  const size_t bulk = p->prec == ACE_FP64 ? 8 : 4;
+  if (np <= most || (size_t)k * p->npts * bulk <= ((size_t)384 << 20)) {
+    for (size_t c = 0; c < np; c += most) first.push_back((int)c);
+  } else {
+    std::vector<int> ord(np);
+    for (size_t q = 0; q < np; ++q) ord[q] = (int)q;
+    auto tile = [&](int q) { return (packs[q].a / B) * (k / B + 1) + packs[q].b / B; };
+    std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return tile(x) < tile(y); });
+    std::vector<Pack> sp(np);
+    std::vector<double> sw(weight.size());
+    std::vector<int> sc(code ? code->size() : 0);
+    for (size_t q = 0; q < np; ++q) {
+      sp[q] = packs[ord[q]];
+      if (split) {
+        sc[2 * q] = (*code)[2 * ord[q]];
+        sc[2 * q + 1] = (*code)[2 * ord[q] + 1];
+      } else if (code) {
+        sc[q] = (*code)[ord[q]];
+      } else {
+        sw[q] = weight[ord[q]];
+      }
+    }
+    packs.swap(sp);
+    weight.swap(sw);
+    if (code) code->swap(sc);
+    // launches: runs of whole tiles up to what the scratch holds
+    size_t start = 0;
+    for (size_t q = 0; q < np;) {
+      size_t e = q;
+      while (e < np && e - q < most && tile((int)e) == tile((int)q)) ++e;
+      if (e - start > most) {
+        first.push_back((int)start);
+        start = q;
+      }
+      q = e;
+    }
+    if (np > start) first.push_back((int)start);
+  }
+  first.push_back((int)np);
 }
 
 bool overlaps(const void* a, size_t na, const void* b, size_t nb) {
@@ -1082,9 +1123,9 @@ int exx_energy(const ace_plan* p, void* stream, void* ws, size_t ws_bytes, const
   double* epart = reinterpret_cast<double*>(w + p->off_epart);
   double* epack = reinterpret_cast<double*>(w + p->off_epack);
   const double factor = p->omega / ((double)p->npts * (double)p->npts);
-  const bool zxy = acex::energy_zxy(p->n, p->prec);
-  const int parts = pair_e ? acex::pair_energy_parts(p->n) : acex::energy_parts_per_pack(p->n);
-  if (pair_e && np) {
+  const bool split = pair_e && p->prec == ACE_FP64;
+  const int parts = split ? acex::pair_energy_parts(p->n) : acex::energy_parts_per_pack(p->n);
+  if (split && np) {
     // the pairs' overlap integrals (in the Cholesky factor's place)
     ProfScope ps(p, 7, s);
     double* ov = reinterpret_cast<double*>(w + p->off_L);
@@ -1092,25 +1133,25 @@ int exx_energy(const ace_plan* p, void* stream, void* ws, size_t ws_bytes, const
                               reinterpret_cast<double*>(w + p->off_part), p->nsplit, true,
                               nullptr, s);
     if (e != hipSuccess) return hip_fail(e);
-    e = acex::launch_pair_scale(d_packs, d_code, np, ov, p->n_orb, p->prec, s);
+    e = acex::launch_pair_scale(d_packs, d_code, np, ov, p->n_orb, s);
     if (e != hipSuccess) return hip_fail(e);
   }
   for (size_t l = 0; l + 1 < first.size(); ++l) {
     const int c0 = first[l], cnt = first[l + 1] - c0;
     {
       ProfScope ps(p, 0, s);
-      e = acex::launch_fwd_yz(g, phi_bulk, d_packs + c0, cnt, S, s, zxy);
+      e = acex::launch_fwd_yz(g, phi_bulk, d_packs + c0, cnt, S, s);
       if (e != hipSuccess) return hip_fail(e);
     }
     {
       ProfScope ps(p, 9, s);
-      if (pair_e) {
-        e = acex::launch_pair_energy_x(g, S, cnt, epart, zxy, s);
+      if (split) {
+        e = acex::launch_pair_energy_x(g, S, cnt, epart, s);
         if (e != hipSuccess) return hip_fail(e);
         e = acex::launch_pair_energy_reduce(epart, d_packs + c0, cnt, parts, factor,
                                             epack + 2 * (size_t)c0, s);
       } else {
-        e = acex::launch_energy_x(g, S, cnt, epart, zxy, s);
+        e = acex::launch_energy_x(g, S, cnt, epart, first.size() > 2, s);
         if (e != hipSuccess) return hip_fail(e);
         e = acex::launch_energy_reduce(epart, cnt, parts, factor, epack + c0, s);
       }
@@ -1120,7 +1161,8 @@ int exx_energy(const ace_plan* p, void* stream, void* ws, size_t ws_bytes, const
   ProfScope ps(p, 7, s);
   if (np == 0) e = acex::launch_fill_f64(ex, 0.0, 1, s);
   else if (pair_e)
-    e = acex::launch_pair_energies(epack, d_code, 2 * np, p->n_orb, -p->alpha, ex, pair_e, s);
+    e = acex::launch_pair_energies(epack, d_code, (int)code.size(), p->n_orb, -p->alpha, ex,
+                                   pair_e, s);
   else
     e = acex::launch_weighted_sum(epack, d_w, np, ex, s);
   return e == hipSuccess ? ACE_OK : hip_fail(e);

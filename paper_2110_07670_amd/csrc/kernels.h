@@ -100,25 +100,22 @@ hipError_t launch_zinv_list(const GridArgs& g, int block, bool diag, const void*
 // x transforms with the Coulomb multiply between forward and inverse, in place.
 hipError_t launch_poisson_x(const GridArgs& g, void* S, int npack, hipStream_t s);
 // x forward transform and sum of K |Z|^2 per workgroup into part[npack][parts_per_pack].
+// stream: S is read with streaming loads (another forward pass follows).
 hipError_t launch_energy_x(const GridArgs& g, const void* S, int npack, double* part,
-                           bool zxy, hipStream_t s);
-// zxy: S is laid out as launch_fwd_yz's zxy form.
+                           bool stream, hipStream_t s);
 int energy_parts_per_pack(int n);
-// The layout of S for the energy passes: zxy where the forward pass of this
-// grid writes it.
-bool energy_zxy(int n, int prec);
-// The energies of both pairs of every transform, apart: x forward transform
+// The energies of both pairs of every FP64 transform, apart: x forward transform
 // and, with Z = A + i B, A and B the transforms of the two real pair densities,
 // the sums of K |A|^2 and K |B|^2 per workgroup into
 // part[npack][2][pair_energy_parts(n)].
 int pair_energy_parts(int n);
 hipError_t launch_pair_energy_x(const GridArgs& g, const void* S, int npack, double* part,
-                                bool zxy, hipStream_t s);
+                                hipStream_t s);
 // Sets each pack's scale from the pairs' overlap integrals ov [n_orb][n_orb]:
 // the pair with the larger one first (codes, two per pack, swap along), the
 // other scaled up by the power of two that brings it level.
 hipError_t launch_pair_scale(Pack* packs, int* codes, int npack, const double* ov, int n_orb,
-                             int prec, hipStream_t s);
+                             hipStream_t s);
 // Inverse (y,z) transforms back to real space, natural order, in place.
 hipError_t launch_inv_yz(const GridArgs& g, void* S, int npack, hipStream_t s);
 

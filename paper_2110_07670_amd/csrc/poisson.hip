@@ -1519,12 +1519,14 @@ __global__ __launch_bounds__(row_threads<N>()) void k_rows_inv(
 // A workgroup owns C lines that are adjacent in memory (consecutive z
 // positions) and runs length-N transforms along a strided axis:
 //   MODE_POISSON : x lines, forward, * K / N, inverse (in place);
-//   MODE_ENERGY  : x lines, forward, sum K |Z|^2 (S unchanged; streaming
-//                  loads: plain ones evict the orbitals that the next forward
-//                  pass reads, 597 against 468 us per 117 transforms of it);
+//   MODE_ENERGY  : x lines, forward, sum K |Z|^2 (S unchanged);
+//   MODE_ENERGY_NT : the same with streaming loads, where another forward pass
+//                  follows: plain loads evict the orbitals that it reads (96^3
+//                  FP64, 128 orbitals: 547 against 427 us per 117 transforms
+//                  of it);
 //   MODE_FWD     : y lines, forward only, written in position order;
 //   MODE_INV     : y lines, inverse only, natural order.
-enum { MODE_POISSON = 0, MODE_ENERGY = 1, MODE_FWD = 2, MODE_INV = 3 };
+enum { MODE_POISSON = 0, MODE_ENERGY = 1, MODE_FWD = 2, MODE_INV = 3, MODE_ENERGY_NT = 4 };
 
 template <typename T>
 __device__ __forceinline__ double block_sum(double v, double* red) {
@@ -1569,7 +1571,7 @@ __global__ __launch_bounds__((line_threads<N, C>())) void k_lines(
 #pragma unroll
       for (int j1 = 0; j1 < N1; ++j1) {
         const cx<T>* q = &base[(int64_t)(t2 + N2 * j1) * estride + c];
-        v[j1] = MODE == MODE_ENERGY ? ld_stream(q) : *q;
+        v[j1] = MODE == MODE_ENERGY_NT ? ld_stream(q) : *q;
       }
       dft<N1, false>(v);
 #pragma unroll
@@ -1608,7 +1610,7 @@ __global__ __launch_bounds__((line_threads<N, C>())) void k_lines(
         }
       }
     }
-    if constexpr (MODE == MODE_ENERGY) {
+    if constexpr (MODE == MODE_ENERGY || MODE == MODE_ENERGY_NT) {
       const double s = block_sum<T>(acc, red);
       if (tid == 0) part[bid] = s;
       return;
@@ -1647,7 +1649,7 @@ __global__ __launch_bounds__((line_threads<N, C>())) void k_lines(
 // transforms meet in one workgroup: N2 pencils adjacent on the inner axis, and
 // the N2 that hold the opposite frequencies (block b of the positions holds
 // block N1 - b's, in reverse).  Both sides of S are read once.  Half the
-// transforms of one pair each: 96 orbitals at 64^3, 9.13 -> 4.38 ms.
+// transforms of one pair each: 96 orbitals at 64^3 FP64, 9.13 -> 4.38 ms.
 // The two densities are brought level before they share a transform
 // (k_pair_scale), so each one's rounding stays its own size.
 template <int N>
@@ -1746,12 +1748,12 @@ __global__ __launch_bounds__(pair_threads<N>()) void k_pair_energy(
   }
 }
 
-// Scales above 2^kMax (or from a vanishing overlap) are cut: in FP32 the
-// orbitals are of order one and their scaled products stay far from overflow.
+// Scales above 2^kMost (or from a vanishing overlap) are cut: the orbitals are of
+// order one and their scaled products stay far from overflow.
 __global__ __launch_bounds__(256) void k_pair_scale(Pack* __restrict__ packs,
                                                     int* __restrict__ codes, int npack,
-                                                    const double* __restrict__ ov, int n_orb,
-                                                    int most) {
+                                                    const double* __restrict__ ov, int n_orb) {
+  constexpr int kMost = 400;
   const int p = blockIdx.x * 256 + threadIdx.x;
   if (p >= npack) return;
   Pack pk = packs[p];
@@ -1771,7 +1773,7 @@ __global__ __launch_bounds__(256) void k_pair_scale(Pack* __restrict__ packs,
   int e = 0;
   if (sd > 0.0 && sb > sd) {
     const double ratio = sb / sd;
-    e = ratio < 1e300 ? min(ilogb(ratio), most) : most;
+    e = ratio < 1e300 ? min(ilogb(ratio), kMost) : kMost;
   }
   pk.e = kPackUnit + e;
   packs[p] = pk;
@@ -2450,15 +2452,11 @@ static hipError_t inv_y_t(const GridArgs& g, void* S, int npack, hipStream_t s) 
 }
 
 template <typename T, int N, int MODE, int C>
-static void x_launch(const GridArgs& g, void* S, int npack, double* part, hipStream_t s,
-                     bool zxy = false) {
+static void x_launch(const GridArgs& g, void* S, int npack, double* part, hipStream_t s) {
   const cx<T>* tw = static_cast<const cx<T>*>(g.tw);
-  // S[x][ky][kz]: pencils adjacent on kz, outer axis ky; zxy, S[kz][x][ky]:
-  // adjacent on ky, outer axis kz
-  const int64_t es = zxy ? N : (int64_t)N * N, os = zxy ? (int64_t)N * N : N;
   hipLaunchKernelGGL((k_lines<T, N, MODE, C>), dim3((N / C) * N * npack),
                      dim3(line_threads<N, C>()), 0, s, static_cast<cx<T>*>(S), tw, npack, g.npts,
-                     es, os, T(g.g2[0]), T(g.g2[zxy ? 2 : 1]), T(g.g2[zxy ? 1 : 2]),
+                     (int64_t)N * N, (int64_t)N, T(g.g2[0]), T(g.g2[1]), T(g.g2[2]),
                      T(g.kscale), part);
 }
 
@@ -2466,8 +2464,7 @@ static void x_launch(const GridArgs& g, void* S, int npack, double* part, hipStr
 // 32 where they divide N; anything else: the default); the energy pass keeps
 // the default, which fixes its partial-sum layout.
 template <typename T, int N, int MODE>
-static hipError_t x_t(const GridArgs& g, void* S, int npack, double* part, hipStream_t s,
-                      bool zxy = false) {
+static hipError_t x_t(const GridArgs& g, void* S, int npack, double* part, hipStream_t s) {
   if constexpr (MODE == MODE_POISSON) {
     if constexpr (N % 8 == 0 && line_chunk<N>() != 8) {
       if (g.pencils == 8) {
@@ -2482,7 +2479,7 @@ static hipError_t x_t(const GridArgs& g, void* S, int npack, double* part, hipSt
       }
     }
   }
-  x_launch<T, N, MODE, line_chunk<N>()>(g, S, npack, part, s, zxy);
+  x_launch<T, N, MODE, line_chunk<N>()>(g, S, npack, part, s);
   return hipGetLastError();
 }
 
@@ -2634,36 +2631,29 @@ hipError_t launch_poisson_x(const GridArgs& g, void* S, int npack, hipStream_t s
   }
 }
 
+template <typename T, int N>
+static hipError_t energy_x_t(const GridArgs& g, void* S, int npack, double* part, bool stream,
+                             hipStream_t s) {
+  // whole 128-byte lines per workgroup only: a neighbour reads the other half
+  // of a shorter segment's line (120^3 FP32 4.23 ms plain, 4.40 streaming)
+  if constexpr (line_chunk<N>() * sizeof(cx<T>) >= 128)
+    if (stream) return x_t<T, N, MODE_ENERGY_NT>(g, S, npack, part, s);
+  return x_t<T, N, MODE_ENERGY>(g, S, npack, part, s);
+}
+
 hipError_t launch_energy_x(const GridArgs& g, const void* S, int npack, double* part,
-                           bool zxy, hipStream_t s) {
+                           bool stream, hipStream_t s) {
   if (npack <= 0) return hipSuccess;
   void* Sm = const_cast<void*>(S);
   switch (g.n) {
 #define X(N)                                                                  \
   case N:                                                                     \
-    return g.prec == 0 ? x_t<double, N, MODE_ENERGY>(g, Sm, npack, part, s, zxy) \
-                       : x_t<float, N, MODE_ENERGY>(g, Sm, npack, part, s, zxy);
+    return g.prec == 0 ? energy_x_t<double, N>(g, Sm, npack, part, stream, s) \
+                       : energy_x_t<float, N>(g, Sm, npack, part, stream, s);
     ACEX_SIZES(X)
 #undef X
     default: return hipErrorInvalidValue;
   }
-}
-
-// The slab forward kernels are faster in the zxy form (96^3 FP64: 463 against
-// 510 us per 128 transforms), whose stores run along whole ky rows; the energy
-// pass reads either at the same rate.
-template <typename T>
-static bool energy_zxy_t(int n) {
-  switch (n) {
-#define X(N) \
-  case N: return fwd_slabs<T, N>() || slab3_ok<T, N>();
-    ACEX_SIZES(X)
-#undef X
-    default: return false;
-  }
-}
-bool energy_zxy(int n, int prec) {
-  return prec == 0 ? energy_zxy_t<double>(n) : energy_zxy_t<float>(n);
 }
 
 int pair_energy_parts(int n) {
@@ -2678,23 +2668,21 @@ int pair_energy_parts(int n) {
 
 template <typename T, int N>
 static hipError_t pair_energy_t(const GridArgs& g, const void* S, int npack, double* part,
-                                bool zxy, hipStream_t s) {
-  const int64_t es = zxy ? N : (int64_t)N * N, os = zxy ? (int64_t)N * N : N;
+                                hipStream_t s) {
   hipLaunchKernelGGL((k_pair_energy<T, N>), dim3(pair_items<N>() * npack),
                      dim3(pair_threads<N>()), 0, s, static_cast<const cx<T>*>(S),
-                     static_cast<const cx<T>*>(g.tw), g.npts, es, os, T(g.g2[0]),
-                     T(g.g2[zxy ? 2 : 1]), T(g.g2[zxy ? 1 : 2]), T(g.kscale), part);
+                     static_cast<const cx<T>*>(g.tw), g.npts, (int64_t)N * N, (int64_t)N,
+                     T(g.g2[0]), T(g.g2[1]), T(g.g2[2]), T(g.kscale), part);
   return hipGetLastError();
 }
 
 hipError_t launch_pair_energy_x(const GridArgs& g, const void* S, int npack, double* part,
-                                bool zxy, hipStream_t s) {
+                                hipStream_t s) {
   if (npack <= 0) return hipSuccess;
+  if (g.prec != 0) return hipErrorInvalidValue;
   switch (g.n) {
-#define X(N)                                                                    \
-  case N:                                                                       \
-    return g.prec == 0 ? pair_energy_t<double, N>(g, S, npack, part, zxy, s)    \
-                       : pair_energy_t<float, N>(g, S, npack, part, zxy, s);
+#define X(N) \
+  case N: return pair_energy_t<double, N>(g, S, npack, part, s);
     ACEX_SIZES(X)
 #undef X
     default: return hipErrorInvalidValue;
@@ -2702,10 +2690,10 @@ hipError_t launch_pair_energy_x(const GridArgs& g, const void* S, int npack, dou
 }
 
 hipError_t launch_pair_scale(Pack* packs, int* codes, int npack, const double* ov, int n_orb,
-                             int prec, hipStream_t s) {
+                             hipStream_t s) {
   if (npack <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_pair_scale, dim3((npack + 255) / 256), dim3(256), 0, s, packs, codes,
-                     npack, ov, n_orb, prec == 0 ? 400 : 48);
+                     npack, ov, n_orb);
   return hipGetLastError();
 }
 
