@@ -57,6 +57,7 @@ struct Tile {
   bool complete;        // every pair of the tile kept: canonical pack order
   int orb0, rows;       // its orbital list: rows entries (I), then block entries (J)
   bool merge;           // not a full complete tile: tiles of one column block merge
+  unsigned fresh;       // J orbitals (diagonal: its orbitals) that no earlier tile updates
   int group0, ngroup;   // its transforms in groups of rows (incomplete or partial tiles)
 };
 
@@ -99,6 +100,7 @@ struct BuildTables {
   size_t o_packs = 0, o_meta = 0, o_tw = 0, o_orbs = 0, o_groups = 0, used = 0;
   std::vector<Tile> tiles;
   bool masked = false;
+  bool fill = false;  // W rows that no tile writes before one adds to them: cleared first
 };
 }  // namespace
 
@@ -475,6 +477,36 @@ void build_schedule(const ace_plan* p, const uint8_t* mask, std::vector<Pack>& p
   close();
 }
 
+// Marks in each tile the orbitals of its J list (diagonal: its one list) whose W
+// rows no earlier tile updates: the tile then writes them instead of adding to
+// them, and W need not be cleared first nor read there (without a mask every
+// row's first update is of this kind).  False, with no mark set, where some row
+// is first updated as an I orbital, or never, or a full tile's rows differ.
+bool mark_fresh(const ace_plan* p, const std::vector<int>& meta, const std::vector<int>& orbs,
+                std::vector<Tile>& tiles) {
+  const int B = p->block;
+  std::vector<char> seen(p->n_orb, 0);
+  bool ok = true;
+  for (Tile& t : tiles) {
+    t.fresh = 0;
+    const unsigned use = t.diag ? t.useI : t.useJ;
+    const int* list = orbs.data() + t.orb0;
+    const int* side = t.diag ? list : list + t.rows;
+    if (!t.diag)
+      for (int m = t.pack0; m < t.pack0 + t.npack; ++m) ok = ok && seen[list[meta[m] & 255]];
+    for (int b = 0; b < B; ++b)
+      if (((use >> b) & 1u) && !seen[side[b]]) {
+        t.fresh |= 1u << b;
+        seen[side[b]] = 1;
+      }
+    if (!t.merge) ok = ok && (t.fresh == 0 || t.fresh == use);
+  }
+  for (char c : seen) ok = ok && c;
+  if (!ok)
+    for (Tile& t : tiles) t.fresh = 0;
+  return ok;
+}
+
 // Energy schedule: two pairs (i, j), (i, j') of one row share a transform.  E_x
 // alone (`code` null): off-diagonal pairs do (both halves carry weight 2),
 // diagonal ones go alone.  Every pair's energy wanted: the diagonal pair
@@ -622,6 +654,7 @@ int prepare_tables(const ace_plan* p, const uint8_t* pair_mask, BuildTables& bt)
   std::vector<int> orbs;
   std::vector<acex::TileGroup> groups;
   build_schedule(p, pair_mask, packs, meta, orbs, bt.tiles, groups);
+  bt.fill = !mark_fresh(p, meta, orbs, bt.tiles);
   bt.masked = pair_mask != nullptr;
   const size_t bulk = p->prec == 0 ? 8 : 4;
   bt.o_packs = 0;
@@ -699,8 +732,10 @@ int build_begin(const ace_plan* p, hipStream_t s, char* w, const double* phi,
     if (e != hipSuccess) return hip_fail(e);
     c.phi_bulk = w + p->off_phi32;
   }
-  e = acex::launch_fill_f64(W, 0.0, (int64_t)p->n_orb * p->npts, s);
-  if (e != hipSuccess) return hip_fail(e);
+  if (bt.fill) {
+    e = acex::launch_fill_f64(W, 0.0, (int64_t)p->n_orb * p->npts, s);
+    if (e != hipSuccess) return hip_fail(e);
+  }
   return ACE_OK;
 }
 
@@ -776,15 +811,17 @@ int tile_accumulate(const BuildCtx& c, hipStream_t s, size_t ti, const void* S, 
   const int* t_orbs = c.d_orbs + t.orb0;
   ProfScope ps(p, 3, s);
   if (tile_fused(c, ti)) {
-    e = acex::launch_zinv_acc(g, B, t.diag, S, c.phi_bulk, W, t_orbs, p->alpha, s, S2,
+    const int fresh = (t.fresh ? 1 : 0) | (S2 && c.bt->tiles[tj].fresh ? 2 : 0);
+    e = acex::launch_zinv_acc(g, B, t.diag, S, c.phi_bulk, W, t_orbs, p->alpha, fresh, s, S2,
                               S2 ? c.d_orbs + c.bt->tiles[tj].orb0 : nullptr);
   } else if (tile_list(c, ti)) {
     e = acex::launch_zinv_list(g, B, t.diag, S, c.phi_bulk, W, t_orbs, t_orbs + t.rows,
-                               c.d_groups + t.group0, t.ngroup, t.useI, t.useJ, p->alpha, s);
+                               c.d_groups + t.group0, t.ngroup, t.useI, t.useJ, t.fresh,
+                               p->alpha, s);
   } else {
     e = acex::launch_accumulate(p->prec, B, t.diag, S, c.phi_bulk, W,
                                 full ? nullptr : c.d_meta + t.pack0, t.npack, t_orbs,
-                                t_orbs + t.rows, t.useI, t.useJ, p->alpha, p->npts, s);
+                                t_orbs + t.rows, t.useI, t.useJ, t.fresh, p->alpha, p->npts, s);
   }
   return e == hipSuccess ? ACE_OK : hip_fail(e);
 }
@@ -1398,6 +1435,7 @@ int ace_batch_create(ace_batch** batch, const ace_plan* const* plans,
           sg.npack = tl[r].npack;
           sg.block = p->block;
           sg.diag = tl[r].diag ? 1 : 0;
+          sg.fresh = tl[r].fresh ? 1 : 0;
           sg.item0 = items;
           sg.count = acex::batch_items(q, p->n, tl[r].npack);
           items += sg.count;

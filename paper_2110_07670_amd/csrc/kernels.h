@@ -62,8 +62,10 @@ hipError_t launch_mid(const GridArgs& g, void* S, int npack, hipStream_t s);
 // phi: the orbitals in the bulk precision (FP64, or the FP32 copy).  With
 // S2 (and orbs2) one launch also does a second tile of the same kind whose
 // orbital blocks are disjoint from the first's.
+// fresh, bit 0 (bit 1): the first (second) tile's J orbitals' W rows (diagonal
+// tiles: its orbitals') are written, not added to.
 hipError_t launch_zinv_acc(const GridArgs& g, int block, bool diag, const void* S,
-                           const void* phi, double* W, const int* orbs, double alpha,
+                           const void* phi, double* W, const int* orbs, double alpha, int fresh,
                            hipStream_t s, const void* S2 = nullptr,
                            const int* orbs2 = nullptr);
 // One group of an incomplete tile's transforms: count of them from first (from
@@ -91,12 +93,12 @@ struct TileGroup {
     size_ += (unsigned)packs + 256u;
   }
 };
-// launch_zinv_acc for a tile with pairs missing: useI and useJ as for
+// launch_zinv_acc for a tile with pairs missing: useI, useJ and fresh as for
 // launch_accumulate.
 hipError_t launch_zinv_list(const GridArgs& g, int block, bool diag, const void* S,
                             const void* phi, double* W, const int* orbs, const int* jorbs,
                             const TileGroup* groups, int ngroups, unsigned useI, unsigned useJ,
-                            double alpha, hipStream_t s);
+                            unsigned fresh, double alpha, hipStream_t s);
 // x transforms with the Coulomb multiply between forward and inverse, in place.
 hipError_t launch_poisson_x(const GridArgs& g, void* S, int npack, hipStream_t s);
 // x forward transform and sum of K |Z|^2 per workgroup into part[npack][parts_per_pack].
@@ -125,12 +127,13 @@ hipError_t launch_inv_yz(const GridArgs& g, void* S, int npack, hipStream_t s);
 // meta == nullptr: a full unmasked B x B tile in the canonical a-major order.
 // orbs, jorbs: the tile's orbital indices, I list (several blocks for a merged
 // off-diagonal tile) and J list (full tiles: right after the I list's block);
-// useI / useJ: local orbitals with at least one pair (diagonal / off it).
+// useI / useJ: local orbitals with at least one pair (diagonal / off it); fresh:
+// those of them whose W rows are written, not added to.
 // phi: the orbitals in the bulk precision (FP64, or the FP32 copy).
 hipError_t launch_accumulate(int prec, int block, bool diag, const void* S, const void* phi,
                              double* W, const int* meta, int npack, const int* orbs,
-                             const int* jorbs, unsigned useI, unsigned useJ, double alpha, int64_t npts,
-                             hipStream_t s);
+                             const int* jorbs, unsigned useI, unsigned useJ, unsigned fresh,
+                             double alpha, int64_t npts, hipStream_t s);
 
 // ---- Batches: one persistent launch per pass over the three-pass tiles of
 // many systems of one grid size, bulk precision and block.  A launch drains a work
@@ -153,6 +156,7 @@ struct BatchSeg {
   double alpha;         // pass 2
   int n, npack, block, diag;
   int item0, count;
+  int fresh;            // as for launch_zinv_acc (pass 2)
 };
 // Is a three-pass tile of this grid, bulk precision and block run by the
 // batch kernels?

@@ -767,7 +767,7 @@ template <typename T, int N, int B, bool DIAG, bool ROWS, int NT, bool LOOP = fa
 __device__ __forceinline__ void zinv_item(const cx<T>* __restrict__ S,
                                           const cx<T>* __restrict__ tw, const T* __restrict__ phi,
                                           double* __restrict__ W, const int* __restrict__ orbs,
-                                          double alpha, int64_t npts, int bid,
+                                          double alpha, int64_t npts, int bid, bool fresh,
                                           cx<T>* __restrict__ lds, cx<T>* __restrict__ stw) {
   constexpr int N1 = fft_split<N>::N1, N2 = fft_split<N>::N2, P = N + 1;
   constexpr int G = B / 2, YC = zinv_rows<T, N, ROWS>();
@@ -953,8 +953,12 @@ __device__ __forceinline__ void zinv_item(const cx<T>* __restrict__ S,
   // tell the rows apart), one memory round trip per row
   double wold[B];
 #pragma unroll
-  for (int b = 0; b < B; ++b)
-    wold[b] = __builtin_nontemporal_load(&W[(int64_t)orbs[(DIAG ? 0 : B) + b] * npts + r]);
+  for (int b = 0; b < B; ++b) wold[b] = 0.0;  // fresh: the build's first update of these rows
+  if (!fresh) {
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+      wold[b] = __builtin_nontemporal_load(&W[(int64_t)orbs[(DIAG ? 0 : B) + b] * npts + r]);
+  }
   if (act) {
 #pragma unroll
     for (int b = 0; b < B; ++b)
@@ -979,8 +983,8 @@ template <typename T, int N, int B, bool DIAG>
 __device__ __forceinline__ void zinv_list_item(
     const cx<T>* __restrict__ S, const cx<T>* __restrict__ tw, const T* __restrict__ phi,
     double* __restrict__ W, const int* __restrict__ orbs,
-    const int* __restrict__ jorbs, const TileGroup* __restrict__ groups, int ngroups, unsigned useI, unsigned useJ, double alpha,
-    int64_t npts, int bid, cx<T>* __restrict__ lds, cx<T>* __restrict__ stw) {
+    const int* __restrict__ jorbs, const TileGroup* __restrict__ groups, int ngroups, unsigned useI,
+    unsigned useJ, unsigned fresh, double alpha, int64_t npts, int bid, cx<T>* __restrict__ lds, cx<T>* __restrict__ stw) {
   constexpr int N1 = fft_split<N>::N1, N2 = fft_split<N>::N2, P = N + 1;
   constexpr int G = B / 2, YC = zinv_rows<T, N>(), R = TileGroup::kRows, NT = zinv_threads<T, N>();
   const int tid = threadIdx.x;
@@ -1076,7 +1080,7 @@ __device__ __forceinline__ void zinv_list_item(
   double wold[B];
 #pragma unroll
   for (int b = 0; b < B; ++b)
-    wold[b] = ((use >> b) & 1u) ? __builtin_nontemporal_load(&W[(int64_t)side[b] * npts + r]) : 0.0;
+    wold[b] = (((use & ~fresh) >> b) & 1u) ? __builtin_nontemporal_load(&W[(int64_t)side[b] * npts + r]) : 0.0;
 #pragma unroll
   for (int b = 0; b < B; ++b)
     if ((use >> b) & 1u)
@@ -1087,12 +1091,12 @@ template <typename T, int N, int B, bool DIAG>
 __global__ __launch_bounds__((zinv_threads<T, N>())) void k_zinv_list(
     const cx<T>* __restrict__ S, const cx<T>* __restrict__ tw, const T* __restrict__ phi,
     double* __restrict__ W, const int* __restrict__ orbs,
-    const int* __restrict__ jorbs, const TileGroup* __restrict__ groups, int ngroups, unsigned useI, unsigned useJ, double alpha,
-    int64_t npts) {
+    const int* __restrict__ jorbs, const TileGroup* __restrict__ groups, int ngroups, unsigned useI,
+    unsigned useJ, unsigned fresh, double alpha, int64_t npts) {
   __shared__ cx<T> lds[(B / 2) * zinv_rows<T, N>() * (N + 1)];
   __shared__ cx<T> stw[N];
-  zinv_list_item<T, N, B, DIAG>(S, tw, phi, W, orbs, jorbs, groups, ngroups, useI, useJ, alpha, npts,
-                                blockIdx.x, lds, stw);
+  zinv_list_item<T, N, B, DIAG>(S, tw, phi, W, orbs, jorbs, groups, ngroups, useI, useJ, fresh,
+                                alpha, npts, blockIdx.x, lds, stw);
 }
 
 // One launch may serve two tiles with disjoint orbital blocks (their W rows
@@ -1100,17 +1104,19 @@ __global__ __launch_bounds__((zinv_threads<T, N>())) void k_zinv_list(
 // orbitals orbs2 (nb, the workgroups of one tile, is a multiple of 8, so
 // every workgroup keeps its XCD order).  Two tiles' 2 nb workgroups fill
 // whole rounds of the chip where one tile's leave the last round half empty.
+// fresh: bit 0 (bit 1): nothing was added to the first (second) tile's J rows
+// of W before (diagonal tiles: its rows); they are written without being read.
 template <typename T, int N, int B, bool DIAG, bool ROWS>
 __global__ __launch_bounds__((zinv_threads<T, N, ROWS>())) void k_zinv_acc(
     const cx<T>* __restrict__ S, const cx<T>* __restrict__ tw, const T* __restrict__ phi,
     double* __restrict__ W, const int* __restrict__ orbs, double alpha, int64_t npts,
-    const cx<T>* __restrict__ S2, const int* __restrict__ orbs2, int nb) {
+    const cx<T>* __restrict__ S2, const int* __restrict__ orbs2, int nb, int fresh) {
   __shared__ cx<T> lds[(B / 2) * zinv_rows<T, N, ROWS>() * (N + 1)];
   __shared__ cx<T> stw[N];
   const int second = (int)blockIdx.x >= nb;
   zinv_item<T, N, B, DIAG, ROWS, zinv_threads<T, N, ROWS>()>(
       second ? S2 : S, tw, phi, W, second ? orbs2 : orbs, alpha, npts,
-      (int)blockIdx.x - (second ? nb : 0), lds, stw);
+      (int)blockIdx.x - (second ? nb : 0), ((fresh >> second) & 1) != 0, lds, stw);
 }
 
 // ------------------------------------------------------------------ y/z slabs, forward
@@ -1809,7 +1815,8 @@ template <typename TS, int B, bool DIAG>
 __global__ __launch_bounds__(kAccThreads) void k_accumulate(
     const cx<TS>* __restrict__ S, const TS* __restrict__ phi, double* __restrict__ W,
     const int* __restrict__ meta, int npack, const int* __restrict__ orbs,
-    const int* __restrict__ jorbs, unsigned useI, unsigned useJ, double alpha, int64_t npts) {
+    const int* __restrict__ jorbs, unsigned useI, unsigned useJ, unsigned fresh, double alpha,
+    int64_t npts) {
   __shared__ TS sph[B][kAccThreads];
   __shared__ double sacc[B][kAccThreads];
   const int t = threadIdx.x;
@@ -1873,7 +1880,7 @@ __global__ __launch_bounds__(kAccThreads) void k_accumulate(
   double wold[B];
 #pragma unroll
   for (int b = 0; b < B; ++b)
-    wold[b] = ((use >> b) & 1u) ? __builtin_nontemporal_load(&W[(int64_t)side[b] * npts + r]) : 0.0;
+    wold[b] = (((use & ~fresh) >> b) & 1u) ? __builtin_nontemporal_load(&W[(int64_t)side[b] * npts + r]) : 0.0;
 #pragma unroll
   for (int b = 0; b < B; ++b)
     if ((use >> b) & 1u)
@@ -1883,7 +1890,7 @@ __global__ __launch_bounds__(kAccThreads) void k_accumulate(
 template <typename TS, int B, bool DIAG>
 __global__ __launch_bounds__(256) void k_accumulate_full(
     const cx<TS>* __restrict__ S, const TS* __restrict__ phi, double* __restrict__ W,
-    const int* __restrict__ orbs, double alpha, int64_t npts) {
+    const int* __restrict__ orbs, bool fresh, double alpha, int64_t npts) {
   const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (r >= npts) return;
   static_assert(DIAG || B % 2 == 0, "off-diagonal rows pack evenly");
@@ -1926,10 +1933,10 @@ __global__ __launch_bounds__(256) void k_accumulate_full(
   // every W row read before any is written (one round trip, not one per row)
   double wI[B], wJ[DIAG ? 1 : B];
 #pragma unroll
-  for (int a = 0; a < B; ++a) wI[a] = W[(int64_t)orbs[a] * npts + r];
+  for (int a = 0; a < B; ++a) wI[a] = DIAG && fresh ? 0.0 : W[(int64_t)orbs[a] * npts + r];
   if constexpr (!DIAG) {
 #pragma unroll
-    for (int b = 0; b < B; ++b) wJ[b] = W[(int64_t)orbs[B + b] * npts + r];
+    for (int b = 0; b < B; ++b) wJ[b] = fresh ? 0.0 : W[(int64_t)orbs[B + b] * npts + r];
   }
 #pragma unroll
   for (int a = 0; a < B; ++a) W[(int64_t)orbs[a] * npts + r] = wI[a] - alpha * accI[a];
@@ -2066,10 +2073,10 @@ __device__ __forceinline__ void batch_item(const BatchSeg& g, int local, cx<T>* 
     const T* phi = static_cast<const T*>(g.phi);
     if (g.diag)
       zinv_item<T, N, B, true, false, NT, true>(S, tw, phi, g.W, g.orbs, g.alpha, g.npts, local,
-                                                smem, stw);
+                                                g.fresh != 0, smem, stw);
     else
       zinv_item<T, N, B, false, false, NT, true>(S, tw, phi, g.W, g.orbs, g.alpha, g.npts, local,
-                                                 smem, stw);
+                                                 g.fresh != 0, smem, stw);
   }
 }
 
@@ -2384,8 +2391,8 @@ static hipError_t mid_t(const GridArgs& g, void* S, int npack, hipStream_t s) {
 
 template <typename T, int N, int B, bool ROWS>
 static hipError_t zinv_launch(const GridArgs& g, bool diag, const void* S, const void* phi,
-                              double* W, const int* orbs, double alpha, hipStream_t s,
-                              const void* S2, const int* orbs2) {
+                              double* W, const int* orbs, double alpha, int fresh,
+                              hipStream_t s, const void* S2, const int* orbs2) {
   if constexpr (zinv_ok<T, N, B, ROWS>()) {
     const int nb = N * (N / zinv_rows<T, N, ROWS>());
     static_assert((N * (N / zinv_rows<T, N, ROWS>())) % 8 == 0, "whole XCD groups per tile");
@@ -2395,11 +2402,11 @@ static hipError_t zinv_launch(const GridArgs& g, bool diag, const void* S, const
     if (diag)
       hipLaunchKernelGGL((k_zinv_acc<T, N, B, true, ROWS>), grid, block, 0, s,
                          static_cast<const cx<T>*>(S), static_cast<const cx<T>*>(g.tw),
-                         static_cast<const T*>(phi), W, orbs, alpha, g.npts, s2, o2, nb);
+                         static_cast<const T*>(phi), W, orbs, alpha, g.npts, s2, o2, nb, fresh);
     else
       hipLaunchKernelGGL((k_zinv_acc<T, N, B, false, ROWS>), grid, block, 0, s,
                          static_cast<const cx<T>*>(S), static_cast<const cx<T>*>(g.tw),
-                         static_cast<const T*>(phi), W, orbs, alpha, g.npts, s2, o2, nb);
+                         static_cast<const T*>(phi), W, orbs, alpha, g.npts, s2, o2, nb, fresh);
     return hipGetLastError();
   }
   return hipErrorInvalidValue;
@@ -2407,30 +2414,30 @@ static hipError_t zinv_launch(const GridArgs& g, bool diag, const void* S, const
 
 template <typename T, int N, int B>
 static hipError_t zinv_t(const GridArgs& g, bool diag, const void* S, const void* phi,
-                         double* W, const int* orbs, double alpha, hipStream_t s,
+                         double* W, const int* orbs, double alpha, int fresh, hipStream_t s,
                          const void* S2, const int* orbs2) {
   if constexpr (zinv_ok<T, N, B, false>())
-    return zinv_launch<T, N, B, false>(g, diag, S, phi, W, orbs, alpha, s, S2, orbs2);
+    return zinv_launch<T, N, B, false>(g, diag, S, phi, W, orbs, alpha, fresh, s, S2, orbs2);
   else
-    return zinv_launch<T, N, B, true>(g, diag, S, phi, W, orbs, alpha, s, S2, orbs2);
+    return zinv_launch<T, N, B, true>(g, diag, S, phi, W, orbs, alpha, fresh, s, S2, orbs2);
 }
 
 template <typename T, int N, int B>
 static hipError_t zinv_list_t(const GridArgs& g, bool diag, const void* S, const void* phi,
                               double* W, const int* orbs, const int* jorbs,
                               const TileGroup* groups, int ngroups,
-                              unsigned useI, unsigned useJ, double alpha, hipStream_t s) {
+                              unsigned useI, unsigned useJ, unsigned fresh, double alpha, hipStream_t s) {
   if constexpr (zinv_ok<T, N, B>()) {
     const dim3 grid(N * (N / zinv_rows<T, N>())), block(zinv_threads<T, N>());
     if (diag)
       hipLaunchKernelGGL((k_zinv_list<T, N, B, true>), grid, block, 0, s,
                          static_cast<const cx<T>*>(S), static_cast<const cx<T>*>(g.tw),
-                         static_cast<const T*>(phi), W, orbs, jorbs, groups, ngroups, useI, useJ, alpha,
+                         static_cast<const T*>(phi), W, orbs, jorbs, groups, ngroups, useI, useJ, fresh, alpha,
                          g.npts);
     else
       hipLaunchKernelGGL((k_zinv_list<T, N, B, false>), grid, block, 0, s,
                          static_cast<const cx<T>*>(S), static_cast<const cx<T>*>(g.tw),
-                         static_cast<const T*>(phi), W, orbs, jorbs, groups, ngroups, useI, useJ, alpha,
+                         static_cast<const T*>(phi), W, orbs, jorbs, groups, ngroups, useI, useJ, fresh, alpha,
                          g.npts);
     return hipGetLastError();
   }
@@ -2570,20 +2577,18 @@ hipError_t launch_mid(const GridArgs& g, void* S, int npack, hipStream_t s) {
 }
 
 hipError_t launch_zinv_acc(const GridArgs& g, int block, bool diag, const void* S,
-                           const void* phi, double* W, const int* orbs, double alpha,
+                           const void* phi, double* W, const int* orbs, double alpha, int fresh,
                            hipStream_t s, const void* S2, const int* orbs2) {
   switch (g.n) {
-#define X(N)                                                                                 \
-  case N:                                                                                    \
-    if (block == 16)                                                                         \
-      return g.prec == 0 ? zinv_t<double, N, 16>(g, diag, S, phi, W, orbs, alpha, s, S2, orbs2) \
-                         : zinv_t<float, N, 16>(g, diag, S, phi, W, orbs, alpha, s, S2, orbs2); \
-    if (block == 8)                                                                          \
-      return g.prec == 0 ? zinv_t<double, N, 8>(g, diag, S, phi, W, orbs, alpha, s, S2, orbs2)  \
-                         : zinv_t<float, N, 8>(g, diag, S, phi, W, orbs, alpha, s, S2, orbs2);  \
+#define Y(T, N, B) zinv_t<T, N, B>(g, diag, S, phi, W, orbs, alpha, fresh, s, S2, orbs2)
+#define X(N)                                                                  \
+  case N:                                                                     \
+    if (block == 16) return g.prec == 0 ? Y(double, N, 16) : Y(float, N, 16); \
+    if (block == 8) return g.prec == 0 ? Y(double, N, 8) : Y(float, N, 8);    \
     return hipErrorInvalidValue;
     ACEX_SIZES(X)
 #undef X
+#undef Y
     default: return hipErrorInvalidValue;
   }
 }
@@ -2591,10 +2596,10 @@ hipError_t launch_zinv_acc(const GridArgs& g, int block, bool diag, const void* 
 hipError_t launch_zinv_list(const GridArgs& g, int block, bool diag, const void* S,
                             const void* phi, double* W, const int* orbs, const int* jorbs,
                             const TileGroup* groups, int ngroups, unsigned useI, unsigned useJ,
-                            double alpha, hipStream_t s) {
+                            unsigned fresh, double alpha, hipStream_t s) {
   switch (g.n) {
 #define Y(T, N, B) \
-  zinv_list_t<T, N, B>(g, diag, S, phi, W, orbs, jorbs, groups, ngroups, useI, useJ, alpha, s)
+  zinv_list_t<T, N, B>(g, diag, S, phi, W, orbs, jorbs, groups, ngroups, useI, useJ, fresh, alpha, s)
 #define X(N)                                                              \
   case N:                                                                 \
     if (block == 16) return g.prec == 0 ? Y(double, N, 16) : Y(float, N, 16); \
@@ -2700,43 +2705,44 @@ hipError_t launch_pair_scale(Pack* packs, int* codes, int npack, const double* o
 template <typename TS, int B>
 static hipError_t acc_t(bool diag, const void* S, const void* phi_v, double* W, const int* meta,
                         int npack, const int* orbs, const int* jorbs, unsigned useI,
-                        unsigned useJ, double alpha, int64_t npts, hipStream_t s) {
+                        unsigned useJ, unsigned fresh, double alpha, int64_t npts,
+                        hipStream_t s) {
   const TS* phi = static_cast<const TS*>(phi_v);
   if (meta == nullptr) {
     const dim3 grid((unsigned)((npts + 255) / 256));
     if (diag)
       hipLaunchKernelGGL((k_accumulate_full<TS, B, true>), grid, dim3(256), 0, s,
-                         static_cast<const cx<TS>*>(S), phi, W, orbs, alpha, npts);
+                         static_cast<const cx<TS>*>(S), phi, W, orbs, fresh != 0, alpha, npts);
     else
       hipLaunchKernelGGL((k_accumulate_full<TS, B, false>), grid, dim3(256), 0, s,
-                         static_cast<const cx<TS>*>(S), phi, W, orbs, alpha, npts);
+                         static_cast<const cx<TS>*>(S), phi, W, orbs, fresh != 0, alpha, npts);
     return hipGetLastError();
   }
   const dim3 grid((unsigned)((npts + kAccThreads - 1) / kAccThreads));
   if (diag)
     hipLaunchKernelGGL((k_accumulate<TS, B, true>), grid, dim3(kAccThreads), 0, s,
-                       static_cast<const cx<TS>*>(S), phi, W, meta, npack, orbs, jorbs, useI, useJ,
+                       static_cast<const cx<TS>*>(S), phi, W, meta, npack, orbs, jorbs, useI, useJ, fresh,
                        alpha, npts);
   else
     hipLaunchKernelGGL((k_accumulate<TS, B, false>), grid, dim3(kAccThreads), 0, s,
-                       static_cast<const cx<TS>*>(S), phi, W, meta, npack, orbs, jorbs, useI, useJ,
+                       static_cast<const cx<TS>*>(S), phi, W, meta, npack, orbs, jorbs, useI, useJ, fresh,
                        alpha, npts);
   return hipGetLastError();
 }
 
 hipError_t launch_accumulate(int prec, int block, bool diag, const void* S, const void* phi,
                              double* W, const int* meta, int npack, const int* orbs,
-                             const int* jorbs, unsigned useI, unsigned useJ, double alpha,
-                             int64_t npts, hipStream_t s) {
+                             const int* jorbs, unsigned useI, unsigned useJ, unsigned fresh,
+                             double alpha, int64_t npts, hipStream_t s) {
   if (block == 16)
-    return prec == 0 ? acc_t<double, 16>(diag, S, phi, W, meta, npack, orbs, jorbs, useI, useJ, alpha,
+    return prec == 0 ? acc_t<double, 16>(diag, S, phi, W, meta, npack, orbs, jorbs, useI, useJ, fresh, alpha,
                                          npts, s)
-                     : acc_t<float, 16>(diag, S, phi, W, meta, npack, orbs, jorbs, useI, useJ, alpha,
+                     : acc_t<float, 16>(diag, S, phi, W, meta, npack, orbs, jorbs, useI, useJ, fresh, alpha,
                                         npts, s);
   if (block == 8)
-    return prec == 0 ? acc_t<double, 8>(diag, S, phi, W, meta, npack, orbs, jorbs, useI, useJ, alpha,
+    return prec == 0 ? acc_t<double, 8>(diag, S, phi, W, meta, npack, orbs, jorbs, useI, useJ, fresh, alpha,
                                         npts, s)
-                     : acc_t<float, 8>(diag, S, phi, W, meta, npack, orbs, jorbs, useI, useJ, alpha,
+                     : acc_t<float, 8>(diag, S, phi, W, meta, npack, orbs, jorbs, useI, useJ, fresh, alpha,
                                        npts, s);
   return hipErrorInvalidValue;
 }

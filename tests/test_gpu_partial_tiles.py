@@ -74,3 +74,35 @@ def test_partial_tile_large_planes(lib, n, k):
     rng = np.random.default_rng(n)
     phi = rng.standard_normal((k, n, n, n)) / n ** 1.5
     _check(lib, phi, "fp64", 8 if n == 120 else 16)
+
+
+@pytest.mark.parametrize("four_pass", [False, True], ids=["auto", "four_pass"])
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("masked", [False, True], ids=["all", "masked"])
+def test_w_is_not_read(lib, masked, prec, four_pass):
+    """Rows of W that no earlier tile updates are written, not added to (and
+    cleared first where that does not hold): NaN in the output array before the
+    build never shows.  28 orbitals: full, partial and merged tiles."""
+    import torch
+    print("[gpu-case] W poisoned masked=%s %s four_pass=%s" % (masked, prec, four_pass), flush=True)
+    n, k = 24, 28
+    phi = _fields(n, k, 3)
+    mask = None
+    if masked:
+        mask = np.random.default_rng(8).random((k, k)) < 0.3
+        mask[:, 20] = mask[20] = False
+        mask[:16, :16] = True
+    plan = lib.Plan(n, (7.0, 8.0, 9.0), k, prec, 0.25)
+    plan.set_tiling(8)
+    plan.set_schedule(four_pass)
+    phi_d = torch.from_numpy(phi).to("cuda:0")
+    ref = lib.ace_build(plan, phi_d, mask)
+    W, xi = torch.full_like(phi_d, float("nan")), torch.empty_like(phi_d)
+    M = torch.empty((k, k), dtype=torch.float64, device="cuda:0")
+    ex = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+    info = torch.zeros(1, dtype=torch.int32, device="cuda:0")
+    lib.build_into(plan, phi_d, W, M, xi, ex, info, lib.workspace(plan.workspace_bytes()), mask)
+    torch.cuda.synchronize()
+    assert torch.equal(W, ref["W"]) and torch.isfinite(W).all()
+    want = O.apply_vx(phi, np.diag([7.0, 8.0, 9.0]), 0.25, mask)
+    assert O.rel_err(W.cpu().numpy(), want) < (1e-10 if prec == "fp64" else 1e-6)
