@@ -819,36 +819,49 @@ __device__ __forceinline__ void zinv_item(const cx<T>* __restrict__ S,
   }
   __syncthreads();
 
-  // inverse z step 2, tasks (c, k1, m) with c fastest, Q2 per thread.  With
-  // FP32 transforms the loads of row a + 1 are issued before row a's W update
-  // so that they are in flight while it runs (the barriers order LDS only);
-  // with FP64 ones the registers for that do not fit next to the W sums
-  // (measured slower with the spills) and each row loads at its start, with
-  // streaming loads in the plane form (4% faster at 96^3; the row form and
-  // the prefetched FP32 form measured slower with them: 42 to 77 ms per
-  // build at 120^3).  With
-  // the prefetch the four-step twiddles are applied at the end of step 2,
-  // which keeps step 1 light; without it, at the start of step 1.
+  // inverse z step 2, tasks (c, k1, m) with c fastest, Q2 per thread.  The
+  // pass is bound by the latency of its row loads: a row is one round trip,
+  // and B rows follow one another.  Row a + 1 is therefore loaded while row a
+  // runs (the barriers order LDS only), from the point where row a's values
+  // have left their registers, the end of step 2.  FP32 holds the whole row;
+  // issued ahead of step 1's barrier, against after step 1 (off-diagonal,
+  // us): 96^3 862 to 781, 80^3 566 to 491, 64^3 250 to 239, 120^3 1743 to
+  // 1553.  With 1024 threads the registers are fewer, and behind that barrier
+  // is better (128^3: 2030 to 1934; ahead 1960).  FP64 has room next to the W
+  // sums for a part of a row only, NP of its N2 values, where a thread has
+  // one task a row: 96^3 609 us with none, 569 with 3, 562 with 5, 652 with
+  // 6 (spills); 80^3 402, 366, 352, 352.  At N = 64 that holds off the
+  // diagonal (170 to 159); on it the registers cost the second workgroup of a
+  // CU (89 to 107).  At N <= 48 four workgroups a CU hide the loads by
+  // themselves (49 to 70 with a prefetch).  The rest of an FP64 row loads at
+  // its start.  The plane form's FP64 loads are streaming (4% faster at 96^3;
+  // the row form and FP32 are slower with them: 42 to 77 ms per build at
+  // 120^3).  With FP32 the four-step twiddles are applied at the end of step
+  // 2, which keeps step 1 light; with FP64, at the start of step 1.
   constexpr int T2MAX = YC * N1 * G;
   // every thread has exactly one step-2 task in every row: no bounds test
   constexpr bool EXACT = !DIAG && T2MAX == NT;
   constexpr bool PF = sizeof(T) == 4;
   constexpr int Q2 = PF ? (T2MAX + NT - 1) / NT : 1;
-  cx<T> pre[Q2][N2];
+  constexpr int NP = PF ? N2 : (T2MAX == NT && !ROWS && N >= (DIAG ? 80 : 64)) ? 5 : 0;
+  constexpr bool EARLY = NT < 1024;
+  static_assert(NP <= N2, "a part of a row's values");
+  cx<T> pre[Q2][NP > 0 ? NP : 1];
   auto fetch = [&](int q0n, int gan) __attribute__((always_inline)) {
 #pragma unroll
-    for (int q = 0; q < Q2; ++q) {
+    for (int q = 0; q < (NP > 0 ? Q2 : 0); ++q) {
       const int task = tid + q * NT;
       if (EXACT || task < YC * N1 * gan) {
         int cc, k1, m;
         task_map(task, cc, k1, m);
         const cx<T>* __restrict__ src = sx + (int64_t)(q0n + m) * npts + cc * CS;
 #pragma unroll
-        for (int t = 0; t < N2; ++t) pre[q][t] = src[(int64_t)(t + N2 * k1) * KS];
+        for (int t = 0; t < NP; ++t)
+          pre[q][t] = PF ? src[(int64_t)(t + N2 * k1) * KS] : ld_stream(&src[(int64_t)(t + N2 * k1) * KS]);
       }
     }
   };
-  if constexpr (PF) fetch(0, DIAG ? (B + 1) / 2 : G);
+  fetch(0, DIAG ? (B + 1) / 2 : G);
 
   int q0 = 0;  // first transform of row a
 #pragma unroll 1
@@ -883,13 +896,22 @@ __device__ __forceinline__ void zinv_item(const cx<T>* __restrict__ S,
         cx<T> v[N2];
 #pragma unroll
         for (int t = 0; t < N2; ++t)
-          v[t] = ROWS ? src[(int64_t)(t + N2 * k1) * KS] : ld_stream(&src[(int64_t)(t + N2 * k1) * KS]);
+          v[t] = t < NP ? pre[0][t < NP ? t : 0]
+                 : ROWS ? src[(int64_t)(t + N2 * k1) * KS]
+                        : ld_stream(&src[(int64_t)(t + N2 * k1) * KS]);
         dft<N2, true>(v);
 #pragma unroll
         for (int t = 0; t < N2; ++t) lds[(m * YC + cc) * P + t + N2 * k1] = v[t];
       }
     }
+    auto issue = [&]() __attribute__((always_inline)) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (a + 1 < B) fetch(q0 + ga, DIAG ? (B - a) / 2 : G);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (NP > 0 && EARLY) issue();
     lds_barrier();
+    if constexpr (NP > 0 && !EARLY) issue();
     // inverse z step 1 to natural z: tasks (t2, c, m), t2 fastest; in the
     // plane form then m (the row offset of a transform, 8 rows of the odd
     // pitch, keeps the two halves of each 16 lanes on distinct banks), in the
@@ -909,11 +931,6 @@ __device__ __forceinline__ void zinv_item(const cx<T>* __restrict__ S,
       for (int j1 = 0; j1 < N1; ++j1) lds[(m * YC + cc) * P + t2 + N2 * j1] = v[j1];
     }
     lds_barrier();
-    if constexpr (PF) {
-      __builtin_amdgcn_sched_barrier(0);
-      if (a + 1 < B) fetch(q0 + ga, DIAG ? (B - a) / 2 : G);
-      __builtin_amdgcn_sched_barrier(0);
-    }
     if constexpr (!DIAG) {
       double accA = 0.0;
 #pragma unroll
