@@ -257,8 +257,11 @@ int ace_plan_tiling(const ace_plan *plan, int *block, int *chunk, int *pencils);
  * at a time so that several workgroups share a compute unit), or where a
  * workgroup can take a plane slab by slab (FP64 120^3 and 128^3, block 8),
  * and four elsewhere; in all of these the
- * inverse z transform feeds the W update directly.  Every other tile takes
- * four passes with the W update a pass of its own.
+ * inverse z transform feeds the W update directly.  Every other tile
+ * (ragged, or with pairs masked out) takes the three passes too in FP64 up
+ * to 120^3, where the full tiles do, and in FP32 from 40^3 to 128^3 but for
+ * 120^3 if all of its pairs are kept; else four passes with the W update a
+ * pass of its own.
  * ACE_SCHEDULE_FOUR_PASS: four passes everywhere.  Both give the same result
  * up to rounding (the order of the W sums differs). */
 #define ACE_SCHEDULE_AUTO 0
@@ -268,7 +271,7 @@ int ace_plan_set_schedule(ace_plan *plan, int schedule);
  * byte accounting): *full_tiles is ACE_TILES_THREE_PASS (forward, middle,
  * inverse z with W), ACE_TILES_ROWS_FUSED (forward, x, inverse y, inverse z
  * rows with W) or ACE_TILES_FOUR_PASS (forward, x, inverse y/z, W), the
- * schedule of full tiles; other tiles take four passes.  *plane is 1 where
+ * schedule of full tiles (other tiles: see above).  *plane is 1 where
  * a (y, z) plane fits LDS (a four-pass inverse y/z is one plane pass) and 0
  * where it does not (a four-pass inverse y/z is a line pass plus a row
  * pass); the forward pass moves the same bytes in either case. */

@@ -31,6 +31,7 @@ STAGE_OF = [
     ("k_plane_fwd", "yz_fwd"), ("k_rows_fwd", "yz_fwd"), ("k_slab_fwd", "yz_fwd"),
     ("k_slab_mid", "x_poisson"), ("k_plane_inv", "yz_inv"), ("k_slab_inv", "yz_inv"),
     ("k_rows_inv", "yz_inv"), ("k_accumulate", "w_accumulate"), ("k_zinv_acc", "w_accumulate"),
+    ("k_zinv_list", "w_accumulate"), ("k_pair_energy", "x_energy"),
     ("k_plane_mid", "x_poisson"), ("k_gemm_abt", "abt_product"),
     ("k_reduce_splits", "abt_product"), ("k_gemm_ab", "ab_product"), ("k_chol_left", "cholesky_inv"),
     ("k_tri_inv", "cholesky_inv"),
