@@ -106,3 +106,26 @@ def test_w_is_not_read(lib, masked, prec, four_pass):
     assert torch.equal(W, ref["W"]) and torch.isfinite(W).all()
     want = O.apply_vx(phi, np.diag([7.0, 8.0, 9.0]), 0.25, mask)
     assert O.rel_err(W.cpu().numpy(), want) < (1e-10 if prec == "fp64" else 1e-6)
+
+
+@pytest.mark.parametrize("n,prec", [(64, "fp64"), (80, "fp64"), (96, "fp64"), (48, "fp32"),
+                                    (80, "fp32")])
+def test_full_tiles_rows_ahead(lib, n, prec):
+    """Two diagonal and one off-diagonal full tile of 16 orbitals, where the
+    fused pass loads the next row ahead (in FP64 a part of it), against the
+    four-pass schedule, which has no such loads.  Both transform each pair in
+    about 20 rounded steps and sum 32 terms: FP64 1e-13 normwise, FP32 1e-6."""
+    import torch
+    print("[gpu-case] full tiles n=%d %s" % (n, prec), flush=True)
+    phi = np.random.default_rng(n).standard_normal((32, n, n, n)) / n ** 1.5
+    dphi = torch.from_numpy(phi).to("cuda:0")
+    res = []
+    for four in (False, True):
+        plan = lib.Plan(n, np.array([7.0, 8.0, 9.0]), 32, prec, 0.25)
+        plan.set_tiling(16)
+        plan.set_schedule(four)
+        out = lib.ace_build(plan, dphi)
+        torch.cuda.synchronize()
+        res.append({key: out[key].cpu().numpy() for key in ("W", "M")})
+    for key in ("W", "M"):
+        assert O.rel_err(res[0][key], res[1][key]) < (1e-13 if prec == "fp64" else 1e-6), key
