@@ -833,7 +833,10 @@ __device__ __forceinline__ void zinv_item(const cx<T>* __restrict__ S,
   // 6 (spills); 80^3 402, 366, 352, 352.  At N = 64 that holds off the
   // diagonal (170 to 159); on it the registers cost the second workgroup of a
   // CU (89 to 107).  At N <= 48 four workgroups a CU hide the loads by
-  // themselves (49 to 70 with a prefetch).  The rest of an FP64 row loads at
+  // themselves (49 to 70 with a prefetch).  The 8-orbital tiles of 120^3
+  // (fewer tasks than threads) take 3 values: 358 us with none, 341 with 2,
+  // 334 with 3, 373 with 5; at 128^3 1024 threads leave no registers (426
+  // with none, 463 with 2).  The rest of an FP64 row loads at
   // its start.  The plane form's FP64 loads are streaming (4% faster at 96^3;
   // the row form and FP32 are slower with them: 42 to 77 ms per build at
   // 120^3).  With FP32 the four-step twiddles are applied at the end of step
@@ -843,7 +846,9 @@ __device__ __forceinline__ void zinv_item(const cx<T>* __restrict__ S,
   constexpr bool EXACT = !DIAG && T2MAX == NT;
   constexpr bool PF = sizeof(T) == 4;
   constexpr int Q2 = PF ? (T2MAX + NT - 1) / NT : 1;
-  constexpr int NP = PF ? N2 : (T2MAX == NT && !ROWS && N >= (DIAG ? 80 : 64)) ? 5 : 0;
+  constexpr bool AHEAD16 = T2MAX == NT && N >= (DIAG ? 80 : 64);
+  constexpr bool AHEAD8 = B == 8 && T2MAX <= NT && N > 96 && NT < 1024;
+  constexpr int NP = PF ? N2 : ROWS ? 0 : AHEAD16 ? 5 : AHEAD8 ? 3 : 0;
   constexpr bool EARLY = NT < 1024;
   static_assert(NP <= N2, "a part of a row's values");
   cx<T> pre[Q2][NP > 0 ? NP : 1];
