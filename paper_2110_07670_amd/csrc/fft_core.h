@@ -28,15 +28,42 @@ template <typename T>
 __device__ __forceinline__ cx<T> operator-(cx<T> a, cx<T> b) { return {a.re - b.re, a.im - b.im}; }
 template <typename T>
 __device__ __forceinline__ cx<T> scale(cx<T> a, T s) { return {a.re * s, a.im * s}; }
+
+// a b + c, rounded once
+__device__ __forceinline__ float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double mad(double a, double b, double c) {
+  return __builtin_fma(a, b, c);
+}
+
+// How the sums of two products below are rounded: one product is rounded, the
+// other goes into a fused multiply-add.  Left free, the compiler chooses, and
+// its choice depends on the order of the loads and branches around the
+// transform, so that a change elsewhere in a kernel can move its FP32 results
+// by a rounding.  The other two fix it: a sum of a positive and a negative
+// term fuses the positive one, a sum of two negative terms the one of x.re; of
+// two positive terms the one of x.re (re_first) or of x.im (im_first).
+// FP32 transforms are fixed except where their inputs are products themselves
+// (the pair densities, the Coulomb factor), whose first sums the compiler
+// fuses with those; FP64 is free.
+enum class Sum { free, re_first, im_first };
+template <typename T, Sum SUM>
+constexpr Sum sum_rule = sizeof(T) == 4 ? SUM : Sum::free;
+
 // a * b
-template <typename T>
+template <Sum SUM = Sum::re_first, typename T>
 __device__ __forceinline__ cx<T> cmul(cx<T> a, cx<T> b) {
-  return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
+  if constexpr (sum_rule<T, SUM> == Sum::free)
+    return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
+  else
+    return {mad(a.re, b.re, -(a.im * b.im)), mad(a.im, b.re, a.re * b.im)};
 }
 // a * conj(b)
 template <typename T>
 __device__ __forceinline__ cx<T> cmulc(cx<T> a, cx<T> b) {
-  return {a.re * b.re + a.im * b.im, a.im * b.re - a.re * b.im};
+  if constexpr (sum_rule<T, Sum::re_first> == Sum::free)
+    return {a.re * b.re + a.im * b.im, a.im * b.re - a.re * b.im};
+  else
+    return {mad(a.re, b.re, a.im * b.im), mad(a.im, b.re, -(a.re * b.im))};
 }
 // a * (-i) for the forward sign, a * (+i) for the inverse sign
 template <bool INV, typename T>
@@ -93,7 +120,7 @@ struct TW {
 };
 
 // x * w_N^E with w_N = exp(-2 pi i / N) (forward) or exp(+2 pi i / N) (inverse)
-template <long E, long N, bool INV, typename T>
+template <long E, long N, bool INV, Sum SUM, typename T>
 __device__ __forceinline__ cx<T> twc(cx<T> x) {
   constexpr long e = ((E % N) + N) % N;
   if constexpr (e == 0) {
@@ -107,7 +134,18 @@ __device__ __forceinline__ cx<T> twc(cx<T> x) {
   } else {
     constexpr T c = T(TW<e, N>::v.c);
     constexpr T s = INV ? T(TW<e, N>::v.s) : T(-TW<e, N>::v.s);
-    return {x.re * c - x.im * s, x.re * s + x.im * c};
+    if constexpr (SUM == Sum::free) {
+      return {x.re * c - x.im * s, x.re * s + x.im * c};
+    } else {
+      constexpr bool im = SUM == Sum::im_first;
+      // |c| = |s|: both sums fuse the same one and share the other, rounded
+      constexpr bool shared = 8 * e % N == 0;
+      constexpr bool both_im = INV ? c > 0 && im : c > 0 || im;
+      constexpr bool fuse_im_re = shared ? both_im : c > 0 ? s < 0 && im : s < 0;
+      constexpr bool fuse_im_im = shared ? both_im : c > 0 && (s < 0 || im);
+      return {fuse_im_re ? mad(x.im, -s, x.re * c) : mad(x.re, c, -(x.im * s)),
+              fuse_im_im ? mad(x.im, c, x.re * s) : mad(x.re, s, x.im * c)};
+    }
   }
 }
 
@@ -128,8 +166,9 @@ struct split_of {
 
 // ------------------------------------------------------------------ DFT_R in registers
 // Natural order in and out: a[k] <- sum_n a[n] w_R^(n k); no scaling.
-template <int R, bool INV, typename T>
+template <int R, bool INV, Sum RULE = Sum::re_first, typename T>
 __device__ __forceinline__ void dft(cx<T>* a) {
+  constexpr Sum SUM = sum_rule<T, RULE>;
   if constexpr (R == 1) {
   } else if constexpr (R == 2) {
     cx<T> t = a[0];
@@ -140,12 +179,20 @@ __device__ __forceinline__ void dft(cx<T>* a) {
     constexpr T h = T(0.86602540378443864676);
     cx<T> s = a[1] + a[2];
     cx<T> d = a[1] - a[2];
-    cx<T> m = {a[0].re - T(0.5) * s.re, a[0].im - T(0.5) * s.im};
-    cx<T> r = rot_i<INV>(d);  // -i d (fwd)
-    r = {r.re * h, r.im * h};
-    a[0] = a[0] + s;
-    a[1] = m + r;
-    a[2] = m - r;
+    if constexpr (SUM == Sum::free) {
+      cx<T> m = {a[0].re - T(0.5) * s.re, a[0].im - T(0.5) * s.im};
+      cx<T> r = rot_i<INV>(d);  // -i d (fwd)
+      r = {r.re * h, r.im * h};
+      a[0] = a[0] + s;
+      a[1] = m + r;
+      a[2] = m - r;
+    } else {
+      const cx<T> m = {mad(T(-0.5), s.re, a[0].re), mad(T(-0.5), s.im, a[0].im)};
+      const cx<T> r = rot_i<INV>(d);
+      a[0] = a[0] + s;
+      a[1] = {mad(h, r.re, m.re), mad(h, r.im, m.im)};
+      a[2] = {mad(-h, r.re, m.re), mad(-h, r.im, m.im)};
+    }
   } else if constexpr (R == 4) {
     cx<T> s02 = a[0] + a[2], d02 = a[0] - a[2];
     cx<T> s13 = a[1] + a[3], d13 = rot_i<INV>(a[1] - a[3]);
@@ -158,10 +205,19 @@ __device__ __forceinline__ void dft(cx<T>* a) {
     constexpr T s1 = T(TW<1, 5>::v.s), s2 = T(TW<2, 5>::v.s);
     cx<T> b1 = a[1] + a[4], b2 = a[2] + a[3];
     cx<T> d1 = a[1] - a[4], d2 = a[2] - a[3];
-    cx<T> t1 = {a[0].re + c1 * b1.re + c2 * b2.re, a[0].im + c1 * b1.im + c2 * b2.im};
-    cx<T> t2 = {a[0].re + c2 * b1.re + c1 * b2.re, a[0].im + c2 * b1.im + c1 * b2.im};
-    cx<T> u1 = {s1 * d1.re + s2 * d2.re, s1 * d1.im + s2 * d2.im};
-    cx<T> u2 = {s2 * d1.re - s1 * d2.re, s2 * d1.im - s1 * d2.im};
+    // c1 b1 + c2 b2 + a0 and the like, rounded as Sum says
+    auto even = [](T p, T x, T q, T y, T z) __attribute__((always_inline)) {
+      if constexpr (SUM == Sum::free) return z + p * x + q * y;
+      else return mad(q, y, mad(p, x, z));
+    };
+    auto odd = [](T p, T x, T q, T y) __attribute__((always_inline)) {
+      if constexpr (SUM == Sum::free) return p * x + q * y;
+      else return q > T(0) ? mad(q, y, p * x) : mad(p, x, q * y);
+    };
+    cx<T> t1 = {even(c1, b1.re, c2, b2.re, a[0].re), even(c1, b1.im, c2, b2.im, a[0].im)};
+    cx<T> t2 = {even(c2, b1.re, c1, b2.re, a[0].re), even(c2, b1.im, c1, b2.im, a[0].im)};
+    cx<T> u1 = {odd(s1, d1.re, s2, d2.re), odd(s1, d1.im, s2, d2.im)};
+    cx<T> u2 = {odd(s2, d1.re, -s1, d2.re), odd(s2, d1.im, -s1, d2.im)};
     u1 = rot_i<INV>(u1);  // -i u1 (fwd)
     u2 = rot_i<INV>(u2);
     a[0] = a[0] + b1 + b2;
@@ -178,17 +234,19 @@ __device__ __forceinline__ void dft(cx<T>* a) {
       constexpr int n2 = decltype(n2c)::value;
       cx<T> t[R1];
       sfor<0, R1>([&](auto n1c) { t[decltype(n1c)::value] = a[n2 + R2 * decltype(n1c)::value]; });
-      dft<R1, INV>(t);
+      dft<R1, INV, SUM>(t);
       sfor<0, R1>([&](auto k1c) {
         constexpr int k1 = decltype(k1c)::value;
-        y[n2 * R1 + k1] = twc<long(n2) * k1, R, INV>(t[k1]);
+        // the odd outputs of a 4-point DFT (real and imaginary parts mixed): im first
+        constexpr Sum S = SUM != Sum::free && R1 == 4 && k1 % 2 == 1 ? Sum::im_first : SUM;
+        y[n2 * R1 + k1] = twc<long(n2) * k1, R, INV, S>(t[k1]);
       });
     });
     sfor<0, R1>([&](auto k1c) {
       constexpr int k1 = decltype(k1c)::value;
       cx<T> t[R2];
       sfor<0, R2>([&](auto n2c) { t[decltype(n2c)::value] = y[decltype(n2c)::value * R1 + k1]; });
-      dft<R2, INV>(t);
+      dft<R2, INV, SUM>(t);
       sfor<0, R2>([&](auto k2c) { a[k1 + R1 * decltype(k2c)::value] = t[decltype(k2c)::value]; });
     });
   }

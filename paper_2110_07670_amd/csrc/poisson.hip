@@ -240,9 +240,9 @@ __device__ __forceinline__ void plane_fwd_loop(Q& q, const cx<T>* __restrict__ t
 #pragma unroll
         for (int j1 = 0; j1 < N1; ++j1)
           v[j1] = {fa[q][j1] * fb[q][j1], fa[q][j1] * (dmask * fd[q][j1])};
-        dft<N1, false>(v);
+        dft<N1, false, Sum::free>(v);
 #pragma unroll
-        for (int k1 = 1; k1 < N1; ++k1) v[k1] = cmul(v[k1], stw[k1 * N2 + t2]);
+        for (int k1 = 1; k1 < N1; ++k1) v[k1] = cmul<Sum::free>(v[k1], stw[k1 * N2 + t2]);
 #pragma unroll
         for (int k1 = 0; k1 < N1; ++k1) lds[y * P + t2 + N2 * k1] = v[k1];
       }
@@ -573,7 +573,7 @@ __device__ __forceinline__ void plane_mid_item(cx<T>* __restrict__ S, const cx<T
 #pragma unroll
     for (int k2 = 0; k2 < N2; ++k2)
       v[k2] = scale(v[k2], coulomb_k<T, N>(k1 + N1 * k2, ky, kz, g0, g1, g2, kscale));
-    dft<N2, true>(v);
+    dft<N2, true, Sum::free>(v);
 #pragma unroll
     for (int t = 0; t < N2; ++t) lds[(t + N2 * k1) * P + py] = v[t];
   }
@@ -772,6 +772,9 @@ __device__ __forceinline__ void zinv_item(const cx<T>* __restrict__ S,
   constexpr int N1 = fft_split<N>::N1, N2 = fft_split<N>::N2, P = N + 1;
   constexpr int G = B / 2, YC = zinv_rows<T, N, ROWS>();
   constexpr int ACT = zinv_threads<T, N, ROWS>();  // threads that own a point
+  // step 2's FP32 sums: the two kinds of tile round them differently (N2 = 6, 10
+  // and 12; no other length has such sums), and keep the values they have had
+  constexpr Sum S2 = DIAG ? Sum::im_first : Sum::re_first;
   static_assert(NT >= ACT, "a thread per point");
   // kz positions and rows in the scratch: S[kz][x][y] (kz stride N^2, rows
   // adjacent) or, with ROWS, S[x][y][kz] (kz adjacent, rows N apart)
@@ -886,7 +889,7 @@ __device__ __forceinline__ void zinv_item(const cx<T>* __restrict__ S,
         if (EXACT || task < YC * N1 * ga) {
           int cc, k1, m;
           task_map(task, cc, k1, m);
-          dft<N2, true>(pre[q]);
+          dft<N2, true, S2>(pre[q]);
           lds[(m * YC + cc) * P + N2 * k1] = pre[q][0];
 #pragma unroll
           for (int t = 1; t < N2; ++t)
@@ -1197,10 +1200,10 @@ __device__ __forceinline__ void slab_fwd_item(const T* __restrict__ phi, const P
             const T fa = pa[off];
             v[j1] = {fa * pb[off], fa * (dmask * pd[off])};
           }
-          dft<N1, false>(v);
+          dft<N1, false, Sum::free>(v);
 #pragma unroll
           for (int k1 = K0; k1 < K0 + SPW * K1S; ++k1) {
-            const cx<T> w = k1 == 0 ? v[0] : cmul(v[k1], stw[k1 * N2 + t2]);
+            const cx<T> w = k1 == 0 ? v[0] : cmul<Sum::free>(v[k1], stw[k1 * N2 + t2]);
             if (k1 < K0 + K1S) lds[y * PZ + t2 + N2 * (k1 - K0)] = w;
             else hold[q][k1 - K0 - K1S] = w;
           }
@@ -1366,7 +1369,7 @@ __device__ __forceinline__ void slab_mid_item(cx<T>* __restrict__ S, int64_t npt
 #pragma unroll
       for (int k2 = 0; k2 < N2; ++k2)
         v[k2] = scale(v[k2], coulomb_k<T, N>(k1 + N1 * k2, ky, kz, g0, g1, g2, kscale));
-      dft<N2, true>(v);
+      dft<N2, true, Sum::free>(v);
 #pragma unroll
       for (int t = 0; t < N2; ++t) lds[(t + N2 * k1) * PZ + py] = v[t];
     }
@@ -1486,9 +1489,9 @@ __global__ __launch_bounds__(row_threads<N>()) void k_rows_fwd(
       const T fa = pa[off];
       v[j1] = {fa * pb[off], fa * (dmask * pd[off])};
     }
-    dft<N1, false>(v);
+    dft<N1, false, Sum::free>(v);
 #pragma unroll
-    for (int k1 = 1; k1 < N1; ++k1) v[k1] = cmul(v[k1], stw[k1 * N2 + t2]);
+    for (int k1 = 1; k1 < N1; ++k1) v[k1] = cmul<Sum::free>(v[k1], stw[k1 * N2 + t2]);
 #pragma unroll
     for (int k1 = 0; k1 < N1; ++k1) lds[y * P + t2 + N2 * k1] = v[k1];
   }
@@ -1632,7 +1635,7 @@ __global__ __launch_bounds__((line_threads<N, C>())) void k_lines(
           }
         }
         if constexpr (MODE == MODE_POISSON) {
-          dft<N2, true>(v);
+          dft<N2, true, Sum::free>(v);
 #pragma unroll
           for (int t = 0; t < N2; ++t) lds[(t + N2 * k1) * C + c] = v[t];
         }
