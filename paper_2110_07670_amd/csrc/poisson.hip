@@ -1912,10 +1912,23 @@ __global__ __launch_bounds__(kAccThreads) void k_accumulate(
       __builtin_nontemporal_store(wold[b] - alpha * sacc[b][t], &W[(int64_t)side[b] * npts + r]);
 }
 
+// FRESH: the J rows of W (diagonal: all) are written, not added to.  A template
+// argument: a choice per row at run time took the FP64 form of 16 orbitals from
+// 133 registers to 512 and 676 bytes of scratch, one wave per SIMD in place of
+// three (64 orbitals at 96^3 in four passes 22.4 ms, 20.7 so).  The FP32 form of
+// 16 orbitals off the diagonal is bound by the latency of its rows: two waves
+// per SIMD with room for more loads in flight, 11.6 against 12.1 ms with three
+// (and 14.6 with one).
 template <typename TS, int B, bool DIAG>
-__global__ __launch_bounds__(256) void k_accumulate_full(
+constexpr int full_waves() {
+  return sizeof(TS) == 4 && B == 16 && !DIAG ? 2 : 8;
+}
+
+template <typename TS, int B, bool DIAG, bool FRESH>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(1, full_waves<TS, B, DIAG>()))) void k_accumulate_full(
     const cx<TS>* __restrict__ S, const TS* __restrict__ phi, double* __restrict__ W,
-    const int* __restrict__ orbs, bool fresh, double alpha, int64_t npts) {
+    const int* __restrict__ orbs, double alpha, int64_t npts) {
   const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (r >= npts) return;
   static_assert(DIAG || B % 2 == 0, "off-diagonal rows pack evenly");
@@ -1958,10 +1971,10 @@ __global__ __launch_bounds__(256) void k_accumulate_full(
   // every W row read before any is written (one round trip, not one per row)
   double wI[B], wJ[DIAG ? 1 : B];
 #pragma unroll
-  for (int a = 0; a < B; ++a) wI[a] = DIAG && fresh ? 0.0 : W[(int64_t)orbs[a] * npts + r];
+  for (int a = 0; a < B; ++a) wI[a] = DIAG && FRESH ? 0.0 : W[(int64_t)orbs[a] * npts + r];
   if constexpr (!DIAG) {
 #pragma unroll
-    for (int b = 0; b < B; ++b) wJ[b] = fresh ? 0.0 : W[(int64_t)orbs[B + b] * npts + r];
+    for (int b = 0; b < B; ++b) wJ[b] = FRESH ? 0.0 : W[(int64_t)orbs[B + b] * npts + r];
   }
 #pragma unroll
   for (int a = 0; a < B; ++a) W[(int64_t)orbs[a] * npts + r] = wI[a] - alpha * accI[a];
@@ -2735,12 +2748,14 @@ static hipError_t acc_t(bool diag, const void* S, const void* phi_v, double* W, 
   const TS* phi = static_cast<const TS*>(phi_v);
   if (meta == nullptr) {
     const dim3 grid((unsigned)((npts + 255) / 256));
-    if (diag)
-      hipLaunchKernelGGL((k_accumulate_full<TS, B, true>), grid, dim3(256), 0, s,
-                         static_cast<const cx<TS>*>(S), phi, W, orbs, fresh != 0, alpha, npts);
-    else
-      hipLaunchKernelGGL((k_accumulate_full<TS, B, false>), grid, dim3(256), 0, s,
-                         static_cast<const cx<TS>*>(S), phi, W, orbs, fresh != 0, alpha, npts);
+#define ACEX_FULL(DIAG, FRESH)                                                      \
+  hipLaunchKernelGGL((k_accumulate_full<TS, B, DIAG, FRESH>), grid, dim3(256), 0, s, \
+                     static_cast<const cx<TS>*>(S), phi, W, orbs, alpha, npts)
+    if (diag && fresh) ACEX_FULL(true, true);
+    else if (diag) ACEX_FULL(true, false);
+    else if (fresh) ACEX_FULL(false, true);
+    else ACEX_FULL(false, false);
+#undef ACEX_FULL
     return hipGetLastError();
   }
   const dim3 grid((unsigned)((npts + kAccThreads - 1) / kAccThreads));
