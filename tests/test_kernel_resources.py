@@ -69,3 +69,24 @@ def test_four_pass_update_keeps_its_waves(kernels):
         assert scratch == 0, (name, scratch)
         assert _waves(regs) >= (2 if name[1:] in {("f", (16, 0, 0)), ("f", (16, 0, 1))} else 3), \
             (name, regs)
+
+
+def _groups(regs, threads):
+    """Workgroups per compute unit that the registers leave."""
+    return 4 * _waves(regs) // (threads // 64)
+
+
+def test_batch_pass_keeps_its_workgroups(kernels):
+    """The persistent inverse-z/W pass fits as many workgroups as the
+    single-system kernels whose work it does (but for 48^3 FP64 in blocks of 8,
+    98 registers against 92: two for three)."""
+    got = [k for k in kernels if k[0] == "k_batch_pass" and k[2][0] == 2]
+    assert got
+    for name in got:
+        _, n, block = name[2]
+        if name[1:] == ("d", (2, 48, 8)):
+            continue
+        own = [kernels["k_zinv_acc", name[1], (n, block, diag, 0)] for diag in (0, 1)]
+        want = min(_groups(regs, threads) for regs, _, threads in own)
+        regs, _, threads = kernels[name]
+        assert _groups(regs, threads) >= want, (name, regs, own)
