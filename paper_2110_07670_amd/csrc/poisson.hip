@@ -125,10 +125,15 @@ __device__ __forceinline__ int opaque_tid() {
   return t;
 }
 
-// the factor of a pack's second pair: a power of two, 0 for a single pair
+// the factor of a pack's second pair: a power of two, 0 for a single pair.  FP64:
+// put together from its bits, in scalar registers (as a call of ldexp it took
+// two vector registers, and the forward pass at 160^3 and 192^3 spilled)
 template <typename T>
 __device__ __forceinline__ T second_scale(const Pack& pk) {
-  return pk.e >= 0 ? T(ldexp(T(1), pk.e - kPackUnit)) : T(0);
+  if constexpr (sizeof(T) == 8)
+    return pk.e >= 0 ? __hiloint2double((pk.e - kPackUnit + 1023) << 20, 0) : 0.0;
+  else
+    return pk.e >= 0 ? T(ldexp(T(1), pk.e - kPackUnit)) : T(0);
 }
 
 template <typename T, int N>

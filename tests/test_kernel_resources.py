@@ -90,3 +90,10 @@ def test_batch_pass_keeps_its_workgroups(kernels):
         want = min(_groups(regs, threads) for regs, _, threads in own)
         regs, _, threads = kernels[name]
         assert _groups(regs, threads) >= want, (name, regs, own)
+
+
+def test_slab_forward_has_no_scratch(kernels):
+    got = {k: v for k, v in kernels.items() if k[0] == "k_slab_fwd"}
+    assert got
+    for name, (_, scratch, _) in got.items():
+        assert scratch == 0, (name, scratch)
