@@ -9,12 +9,13 @@
 namespace acex {
 
 // One packed transform carries two real pairs that share their first orbital,
-// rho = phi_a (phi_b + i 2^(e - kPackUnit) phi_d); e = -1 marks a transform
-// carrying the pair (a, b) alone.
+// rho = phi_a (phi_b + i 2^(e - kPackUnit) phi_d); e < 0 marks a transform
+// carrying the pair (a, b) alone.  Pair energies: kPairZero and kPairNan mark one
+// whose second pair was left out, its density being zero or not finite.
 struct Pack {
   int a, b, e, d;
 };
-constexpr int kPackUnit = 1024;
+constexpr int kPackUnit = 1024, kPairZero = -2, kPairNan = -3;
 
 struct GridArgs {
   int n;              // points per axis (cubic grid)
@@ -115,7 +116,8 @@ hipError_t launch_pair_energy_x(const GridArgs& g, const void* S, int npack, dou
                                 hipStream_t s);
 // Sets each pack's scale from the pairs' overlap integrals ov [n_orb][n_orb]:
 // the pair with the larger one first (codes, two per pack, swap along), the
-// other scaled up by the power of two that brings it level.
+// other scaled up by the power of two that brings it level.  A pair whose
+// overlap is zero or not finite leaves the transform to the other one.
 hipError_t launch_pair_scale(Pack* packs, int* codes, int npack, const double* ov, int n_orb,
                              hipStream_t s);
 // Inverse (y,z) transforms back to real space, natural order, in place.

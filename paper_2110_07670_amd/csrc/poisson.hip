@@ -1792,8 +1792,8 @@ __global__ __launch_bounds__(pair_threads<N>()) void k_pair_energy(
   }
 }
 
-// Scales above 2^kMost (or from a vanishing overlap) are cut: the orbitals are of
-// order one and their scaled products stay far from overflow.
+// Scales above 2^kMost are cut: the orbitals are of order one and their scaled
+// products stay far from overflow.
 __global__ __launch_bounds__(256) void k_pair_scale(Pack* __restrict__ packs,
                                                     int* __restrict__ codes, int npack,
                                                     const double* __restrict__ ov, int n_orb) {
@@ -1803,7 +1803,8 @@ __global__ __launch_bounds__(256) void k_pair_scale(Pack* __restrict__ packs,
   Pack pk = packs[p];
   if (pk.e < 0) return;
   double sb = ov[(int64_t)pk.a * n_orb + pk.b], sd = ov[(int64_t)pk.a * n_orb + pk.d];
-  if (sd > sb) {
+  const bool finite_b = sb < INFINITY, finite_d = sd < INFINITY;  // false for NaN
+  if (finite_d && (!finite_b || sd > sb)) {
     const double t = sb;
     sb = sd;
     sd = t;
@@ -1814,12 +1815,18 @@ __global__ __launch_bounds__(256) void k_pair_scale(Pack* __restrict__ packs,
     codes[2 * p] = codes[2 * p + 1];
     codes[2 * p + 1] = cc;
   }
-  int e = 0;
-  if (sd > 0.0 && sb > sd) {
-    const double ratio = sb / sd;
-    e = ratio < 1e300 ? min(ilogb(ratio), kMost) : kMost;
+  if (finite_b != finite_d) {
+    pk.e = kPairNan;  // a NaN or infinity would spoil the other pair's transform
+  } else if (sd == 0.0) {
+    pk.e = kPairZero;  // not the rounding of the other pair's transform
+  } else {
+    int e = 0;
+    if (sb > sd) {
+      const double ratio = sb / sd;
+      e = ratio < 1e300 ? min(ilogb(ratio), kMost) : kMost;
+    }
+    pk.e = kPackUnit + e;
   }
-  pk.e = kPackUnit + e;
   packs[p] = pk;
 }
 
@@ -2019,7 +2026,8 @@ __global__ void k_pair_energy_reduce(const double* __restrict__ part,
   const double s = block_sum<double>(acc, red);
   if (threadIdx.x == 0) {
     const int x = packs[q / 2].e;
-    e[q] = s * factor * ((q & 1) && x >= 0 ? ldexp(1.0, 2 * (kPackUnit - x)) : 1.0);
+    if ((q & 1) && x < 0) e[q] = x == kPairNan ? __longlong_as_double(0x7ff8000000000000ll) : 0.0;
+    else e[q] = s * factor * ((q & 1) ? ldexp(1.0, 2 * (kPackUnit - x)) : 1.0);
   }
 }
 

@@ -1,0 +1,54 @@
+"""FP64 per-pair energies where the two pairs of a transform must not show in
+each other: a NaN or an infinity in one orbital, and densities that vanish.
+
+Every pair is what it is by itself: NaN where its own density is not finite,
+exactly zero where its density is, and elsewhere numpy's value to 1e-12 (the
+bound of the ordinary pairs: a few eps of a transform whose two densities are
+level).
+"""
+import numpy as np
+import pytest
+
+from tests.test_gpu_pair_energies import _orbitals, _reference, lib  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def _pairs(lib, phi, L):
+    import torch
+    plan = lib.Plan(phi.shape[1], L, phi.shape[0], "fp64", 0.25)
+    _, pe = lib.exx_energy(plan, torch.from_numpy(phi).to("cuda:0"), pair_energies=True)
+    torch.cuda.synchronize()
+    return pe.cpu().numpy()
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("k,where", [(5, 3), (6, 0), (24, 7)])
+def test_not_finite_orbital(lib, k, where, bad):  # noqa: F811
+    print("[gpu-case] pair energies with %s in orbital %d of %d" % (bad, where, k), flush=True)
+    phi, L = _orbitals(32, k, 9)
+    ref = _reference(phi, L, 0.25)
+    phi[where, 1, 2, 3] = bad
+    e = _pairs(lib, phi, L)
+    own = np.zeros((k, k), dtype=bool)
+    own[where] = own[:, where] = True
+    iu = np.triu_indices(k)
+    assert np.all(np.isnan(e[iu]) == own[iu])
+    ok = np.triu(~own)
+    assert np.all(np.abs(e[ok] - ref[ok]) <= 1e-12 * np.abs(ref[ok]))
+
+
+def test_vanishing_densities(lib):  # noqa: F811
+    """Orbitals on slabs that do not meet: their pairs' energies are zero."""
+    print("[gpu-case] pair energies of orbitals that do not meet", flush=True)
+    n, k = 32, 24
+    phi, L = _orbitals(n, k, 4)
+    for i in range(k):
+        keep = np.zeros(n, dtype=bool)
+        keep[np.arange(8) + 8 * (i % 4)] = True
+        phi[i, ~keep] = 0.0
+    e, ref = _pairs(lib, phi, L), _reference(phi, L, 0.25)
+    iu = np.triu_indices(k)
+    apart = (iu[0] % 4) != (iu[1] % 4)
+    assert np.all(e[iu][apart] == 0.0)
+    assert np.all(np.abs(e[iu][~apart] - ref[iu][~apart]) <= 1e-12 * np.abs(ref[iu][~apart]))
