@@ -1792,12 +1792,12 @@ __global__ __launch_bounds__(pair_threads<N>()) void k_pair_energy(
   }
 }
 
-// Scales above 2^kMost are cut: the orbitals are of order one and their scaled
-// products stay far from overflow.
+// Scales above 2^kMost are cut: such a pair's energy, 2^-1200 of the other's, is
+// below the smallest double, and orbitals of up to 1e120 stay finite.
 __global__ __launch_bounds__(256) void k_pair_scale(Pack* __restrict__ packs,
                                                     int* __restrict__ codes, int npack,
                                                     const double* __restrict__ ov, int n_orb) {
-  constexpr int kMost = 400;
+  constexpr int kMost = 600;
   const int p = blockIdx.x * 256 + threadIdx.x;
   if (p >= npack) return;
   Pack pk = packs[p];
@@ -2027,7 +2027,7 @@ __global__ void k_pair_energy_reduce(const double* __restrict__ part,
   if (threadIdx.x == 0) {
     const int x = packs[q / 2].e;
     if ((q & 1) && x < 0) e[q] = x == kPairNan ? __longlong_as_double(0x7ff8000000000000ll) : 0.0;
-    else e[q] = s * factor * ((q & 1) ? ldexp(1.0, 2 * (kPackUnit - x)) : 1.0);
+    else e[q] = (q & 1) ? ldexp(s * factor, 2 * (kPackUnit - x)) : s * factor;
   }
 }
 

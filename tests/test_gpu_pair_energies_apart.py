@@ -52,3 +52,23 @@ def test_vanishing_densities(lib):  # noqa: F811
     apart = (iu[0] % 4) != (iu[1] % 4)
     assert np.all(e[iu][apart] == 0.0)
     assert np.all(np.abs(e[iu][~apart] - ref[iu][~apart]) <= 1e-12 * np.abs(ref[iu][~apart]))
+
+
+def test_far_smaller_pairs(lib):  # noqa: F811
+    """Narrow orbitals along a line: overlaps from 1 down to 1e-140, energies
+    down to 1e-280, each to 1e-12 of itself."""
+    print("[gpu-case] pair energies down to 1e-280", flush=True)
+    n, k, width = 48, 5, 0.75
+    L = np.array([90.0, 18.0, 18.0])
+    x = [L[a] * np.arange(n) / n for a in range(3)]
+    phi = np.zeros((k, n, n, n))
+    for i, place in enumerate((0, 4, 1, 3, 2)):  # (0, 0) and (0, 1) share a transform
+        # 0.3 of the cell apart at most: the images lie farther
+        c = np.array([0.075 * place * L[0], 9.0, 9.0])
+        g = [np.exp(-((x[a] - c[a] - L[a] * np.rint((x[a] - c[a]) / L[a])) / width) ** 2 / 2)
+             for a in range(3)]
+        phi[i] = g[0][:, None, None] * g[1][None, :, None] * g[2][None, None, :]
+    e, ref = _pairs(lib, phi, L), _reference(phi, L, 0.25)
+    iu = np.triu_indices(k)
+    assert np.abs(ref[iu]).min() < 1e-270 and np.all(ref[iu] != 0.0)
+    assert np.all(np.abs(e[iu] - ref[iu]) <= 1e-12 * np.abs(ref[iu])), e[iu] / ref[iu] - 1
