@@ -507,12 +507,34 @@ bool mark_fresh(const ace_plan* p, const std::vector<int>& meta, const std::vect
   return ok;
 }
 
+// Where every pair's energy is wanted, do two pairs share a transform, to be told
+// apart by k_pair_energy?  Not in FP32: the rounding of a shared transform
+// would show in the smaller energy.  In FP64 where the transforms saved, 6 us per
+// million points each, outweigh bringing the pairs level first: the overlap
+// integrals of all orbitals (4 us per orbital and million points, from 120
+// orbitals on n_orb^2 / 30 in matrix instructions) and 10 us of launches.
+// Each pair alone against shared, us: 32^3 x 8 64, 69; 32^3 x 16 95, 85;
+// 48^3 x 8 78, 82; 64^3 x 8 103, 97; 96^3 x 4 108, 113; 96^3 x 8 279, 186;
+// 128^3 x 3 150, 156; 128^3 x 4 212, 186; of 128 orbitals at 96^3 the diagonal
+// alone 960, 1535, 64 pairs of all rows 505, 953, 256 of them 1773, 1735, 1024
+// 6878, 4460.
+bool share_pair_energies(const ace_plan* p, const uint8_t* mask) {
+  if (p->prec != ACE_FP64) return false;
+  int64_t saved = 0;
+  for (int i = 0; i < p->n_orb; ++i) {
+    int kept = 0;
+    for (int j = i; j < p->n_orb; ++j) kept += mask_on(mask, p->n_orb, i, j);
+    saved += kept / 2;
+  }
+  const double k = p->n_orb, npts = (double)p->npts;
+  return 6.0 * (double)saved * npts > 10e6 + npts * std::max(4.0 * k, k * k / 30.0);
+}
+
 // Energy schedule: two pairs (i, j), (i, j') of one row share a transform.  E_x
 // alone (`code` null): off-diagonal pairs do (both halves carry weight 2),
-// diagonal ones go alone.  Every pair's energy wanted: the diagonal pair
-// shares one too, and code[2 p], code[2 p + 1] = i n_orb + j of pack p's pairs
-// (-1: none).  In FP32 each pair then goes alone (code[p]): the rounding of a
-// shared transform would show in the smaller energy.
+// diagonal ones go alone.  Every pair's energy wanted: with `split` the diagonal
+// pair shares one too, and code[2 p], code[2 p + 1] = i n_orb + j of pack p's
+// pairs (-1: none); else each pair goes alone (code[p]).
 // `first`: the first packs of the launches.  Where there are several and the
 // orbitals far exceed the 256 MB last-level cache (40 at 120^3 FP32, 276 MB, are
 // 2% slower so), the packs go tile by tile as in a
@@ -520,10 +542,9 @@ bool mark_fresh(const ace_plan* p, const std::vector<int>& meta, const std::vect
 // (128 orbitals at 96^3 FP64: forward pass 549 us per 128 transforms by rows
 // with the energy pass evicting the orbitals, 427 us per 117 by tiles without).
 void build_energy_schedule(const ace_plan* p, const uint8_t* mask, std::vector<Pack>& packs,
-                           std::vector<double>& weight, std::vector<int>* code,
+                           std::vector<double>& weight, std::vector<int>* code, bool split,
                            std::vector<int>& first) {
   const int k = p->n_orb, B = p->block;
-  const bool split = code && p->prec == ACE_FP64;  // two pairs to tell apart
   packs.clear();
   weight.clear();
   for (int i = 0; i < k; ++i) {
@@ -1117,7 +1138,8 @@ int exx_energy(const ace_plan* p, void* stream, void* ws, size_t ws_bytes, const
   std::vector<Pack> packs;
   std::vector<double> weight;
   std::vector<int> code, first;
-  build_energy_schedule(p, pair_mask, packs, weight, pair_e ? &code : nullptr, first);
+  const bool split = pair_e && share_pair_energies(p, pair_mask);  // two pairs to tell apart
+  build_energy_schedule(p, pair_mask, packs, weight, pair_e ? &code : nullptr, split, first);
   const int np = (int)packs.size();
   const size_t bulk = p->prec == 0 ? 8 : 4;
   const size_t o_packs = 0;
@@ -1160,7 +1182,6 @@ int exx_energy(const ace_plan* p, void* stream, void* ws, size_t ws_bytes, const
   double* epart = reinterpret_cast<double*>(w + p->off_epart);
   double* epack = reinterpret_cast<double*>(w + p->off_epack);
   const double factor = p->omega / ((double)p->npts * (double)p->npts);
-  const bool split = pair_e && p->prec == ACE_FP64;
   const int parts = split ? acex::pair_energy_parts(p->n) : acex::energy_parts_per_pack(p->n);
   if (split && np) {
     // the pairs' overlap integrals (in the Cholesky factor's place)

@@ -1,5 +1,6 @@
 """FP64 per-pair energies where the two pairs of a transform must not show in
-each other: a NaN or an infinity in one orbital, and densities that vanish.
+each other: a NaN or an infinity in one orbital, densities that vanish or are
+far smaller; and pairs that go alone where sharing does not pay.
 
 Every pair is what it is by itself: NaN where its own density is not finite,
 exactly zero where its density is, and elsewhere numpy's value to 1e-12 (the
@@ -58,12 +59,13 @@ def test_far_smaller_pairs(lib):  # noqa: F811
     """Narrow orbitals along a line: overlaps from 1 down to 1e-140, energies
     down to 1e-280, each to 1e-12 of itself."""
     print("[gpu-case] pair energies down to 1e-280", flush=True)
-    n, k, width = 48, 5, 0.75
+    n, k, width = 48, 12, 0.75
     L = np.array([90.0, 18.0, 18.0])
     x = [L[a] * np.arange(n) / n for a in range(3)]
     phi = np.zeros((k, n, n, n))
-    for i, place in enumerate((0, 4, 1, 3, 2)):  # (0, 0) and (0, 1) share a transform
-        # 0.3 of the cell apart at most: the images lie farther
+    # neighbours in the list share a transform: 0.3 of the cell apart at most, so
+    # that the images lie farther
+    for i, place in enumerate((0, 4, 1, 3, 2, 2.5, 0.5, 3.5, 1.5, 0.25, 3.75, 2.25)):
         c = np.array([0.075 * place * L[0], 9.0, 9.0])
         g = [np.exp(-((x[a] - c[a] - L[a] * np.rint((x[a] - c[a]) / L[a])) / width) ** 2 / 2)
              for a in range(3)]
@@ -72,3 +74,49 @@ def test_far_smaller_pairs(lib):  # noqa: F811
     iu = np.triu_indices(k)
     assert np.abs(ref[iu]).min() < 1e-270 and np.all(ref[iu] != 0.0)
     assert np.all(np.abs(e[iu] - ref[iu]) <= 1e-12 * np.abs(ref[iu])), e[iu] / ref[iu] - 1
+
+
+@pytest.mark.parametrize("n,k", [(16, 54), (24, 30), (32, 20), (40, 16), (48, 12), (64, 9),
+                                 (80, 7), (96, 6), (120, 5), (128, 5), (144, 4), (160, 4),
+                                 (192, 4)])
+def test_shared_transforms(lib, n, k):  # noqa: F811
+    """Two pairs per transform on every grid (rows of even and odd length)."""
+    print("[gpu-case] shared pair energies n=%d k=%d" % (n, k), flush=True)
+    phi, L = _orbitals(n, k, 100 + n)
+    plan = lib.Plan(n, L, k, "fp64", 0.25)
+    assert _stage_counts(lib, plan, phi)[7] == 3
+    e, ref = _pairs(lib, phi, L), _reference(phi, L, 0.25)
+    iu = np.triu_indices(k)
+    assert np.all(np.abs(e[iu] - ref[iu]) <= 1e-12 * np.abs(ref[iu]))
+
+
+def _stage_counts(lib, plan, phi, mask=None):
+    import torch
+    plan.set_profiling(True)
+    lib.exx_energy(plan, torch.from_numpy(phi).to("cuda:0"), mask, pair_energies=True)
+    plan.set_profiling(False)
+    return [count for _, count in plan.profile_read().values()]
+
+
+@pytest.mark.parametrize("kind", ["few_orbitals", "diagonal", "few_pairs"])
+def test_alone_where_sharing_does_not_pay(lib, kind):  # noqa: F811
+    """No overlap integrals (a third stage-7 entry beside the tables and the
+    sum) where few or no transforms would be saved."""
+    print("[gpu-case] pair energies alone: %s" % kind, flush=True)
+    n, k = (48, 3) if kind == "few_orbitals" else (48, 24)
+    phi, L = _orbitals(n, k, 12)
+    mask = None
+    if kind == "diagonal":
+        mask = np.eye(k, dtype=bool)
+    if kind == "few_pairs":
+        mask = np.zeros((k, k), dtype=bool)
+        mask[2, 5:9] = mask[7, 11:14] = True
+    plan = lib.Plan(n, L, k, "fp64", 0.25)
+    assert _stage_counts(lib, plan, phi, mask)[7] == 2
+    import torch
+    _, pe = lib.exx_energy(plan, torch.from_numpy(phi).to("cuda:0"), mask, pair_energies=True)
+    torch.cuda.synchronize()
+    e = pe.cpu().numpy()
+    ref = _reference(phi, L, 0.25)
+    ref = np.where(np.triu(np.ones((k, k)) if mask is None else mask), ref, 0.0)
+    assert np.all(np.abs(e - ref) <= 1e-12 * np.abs(ref))
