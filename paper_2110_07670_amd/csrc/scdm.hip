@@ -598,9 +598,9 @@ __global__ __launch_bounds__(256) void k_ns_step(const double* __restrict__ Y,
 }
 
 // Iterations it0 .. iters - 1 in one workgroup, for the rare matrix that the
-// launched iterations leave unfinished (a condition number above about 1e5);
-// exits at once otherwise.  Buffers and err are read and written by one
-// workgroup only, with a barrier between.
+// launched iterations leave unfinished (ns_launched); exits at once otherwise.
+// Buffers and err are read and written by one workgroup only, with a barrier
+// between.
 __global__ __launch_bounds__(1024) void k_ns_tail(double* Y0, double* Y1, double* G, int k,
                                                   int it0, int iters, double* err, int* state) {
   if (state[0] != 0) return;
@@ -715,10 +715,18 @@ hipError_t launch_scdm_qr(const double* phi, const int* points, int m, int k, in
   return hipGetLastError();
 }
 
-// Iterations issued as launches; the rest, up to max_iter, in k_ns_tail.
-// From Y = A / ||A||_F the smallest singular value grows by 1.5 per iteration
-// until it nears 1: 40 iterations reach a condition number of about 1e5.
-constexpr int kNsLaunched = 40;
+// Iterations issued as launches; the rest, up to max_iter, in k_ns_tail.  From
+// Y = A / ||A||_F the smallest singular value grows by 1.5 per iteration until
+// it nears 1, so 40 iterations reach a condition number of about 1e5.  An
+// iteration that finds all done costs 3 us, one of the tail's 0.1 ms at 128
+// orbitals, 0.45 at 192 and 7 at 512, where a launched one takes 10 to 50 us.
+// Past 128 orbitals all are therefore launched (a whole localisation with 256:
+// 3.58 -> 3.76 ms where 20 iterations do, 47.1 -> 4.6 at a condition number of
+// 1e12, 12.7 -> 4.2 at 1e6; with 512 96.5 -> 12.8); from 65 on 48 of them (128
+// at 1e12 7.7 -> 6.8 ms).
+static int ns_launched(int k, int max_iter) {
+  return std::min(k > 128 ? max_iter : k > 64 ? 48 : 40, max_iter);
+}
 
 hipError_t launch_scdm_polar(const double* phi, const int* pivots, int k, int64_t npts, double* Y,
                              double* G, double* Z, double* sq, double* err, int* state, int* info,
@@ -726,15 +734,16 @@ hipError_t launch_scdm_polar(const double* phi, const int* pivots, int k, int64_
   const int T = (k + 15) / 16;
   hipLaunchKernelGGL(k_ns_gather, dim3(k), dim3(256), 0, s, phi, pivots, k, npts, Y, sq);
   hipLaunchKernelGGL(k_ns_init, dim3(k), dim3(256), 0, s, k, sq, Y, max_iter, err, state);
-  const int launched = std::min(kNsLaunched, max_iter);
+  const int launched = ns_launched(k, max_iter);
   for (int it = 0; it < launched; ++it) {
     double* in = (it & 1) ? Z : Y;
     double* out = (it & 1) ? Y : Z;
     hipLaunchKernelGGL(k_ns_gram, dim3(T * (T + 1) / 2), dim3(256), 0, s, in, G, k, it, err, state);
     hipLaunchKernelGGL(k_ns_step, dim3(T * T), dim3(256), 0, s, in, G, out, k, it, err, state);
   }
-  hipLaunchKernelGGL(k_ns_tail, dim3(1), dim3(1024), 0, s, Y, Z, G, k, launched, max_iter, err,
-                     state);
+  if (launched < max_iter)
+    hipLaunchKernelGGL(k_ns_tail, dim3(1), dim3(1024), 0, s, Y, Z, G, k, launched, max_iter, err,
+                       state);
   hipLaunchKernelGGL(k_ns_finish, dim3(k), dim3(256), 0, s, state, max_iter, k, Y, Z, info);
   return hipGetLastError();
 }
