@@ -192,20 +192,11 @@ constexpr int kAbtAhead = 3;
 template <int RM, int WM, int RN, int WN, bool VEC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_gemm_abt(
     const double* __restrict__ A, const double* __restrict__ B, int m, int n, int64_t K,
-    int64_t kchunk, int tiles_n, bool sym, bool abs_in, double* __restrict__ partial,
+    int64_t kchunk, int tiles_n, bool abs_in, double* __restrict__ partial,
     const int* __restrict__ skip) {
   if (skip && *skip != 0) return;
   constexpr int WK = 4 / (WM * WN), TM = 16 * RM * WM, TN = 16 * RN * WN, D = kAbtAhead;
-  int tm, tn;
-  if (sym) {  // the tiles on and below the diagonal, row by row
-    tm = 0;
-    int t = blockIdx.x;
-    while (t > tm) t -= ++tm;
-    tn = t;
-  } else {
-    tm = blockIdx.x / tiles_n;
-    tn = blockIdx.x % tiles_n;
-  }
+  const int tm = blockIdx.x / tiles_n, tn = blockIdx.x % tiles_n;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wk = wave / (WM * WN), wmn = wave % (WM * WN), wm = wmn / WN, wn = wmn % WN;
@@ -368,14 +359,14 @@ int abt_tile(int m) {
 
 template <int RM, int WM, int RN, int WN>
 void abt_launch(bool vec, dim3 grid, hipStream_t s, const double* A, const double* B, int m, int n,
-                int64_t K, int64_t kchunk, int tiles_n, bool sym, bool abs_in, double* partial,
+                int64_t K, int64_t kchunk, int tiles_n, bool abs_in, double* partial,
                 const int* skip) {
   if (vec)
     hipLaunchKernelGGL((k_gemm_abt<RM, WM, RN, WN, true>), grid, dim3(256), 0, s, A, B, m, n, K,
-                       kchunk, tiles_n, sym, abs_in, partial, skip);
+                       kchunk, tiles_n, abs_in, partial, skip);
   else
     hipLaunchKernelGGL((k_gemm_abt<RM, WM, RN, WN, false>), grid, dim3(256), 0, s, A, B, m, n, K,
-                       kchunk, tiles_n, sym, abs_in, partial, skip);
+                       kchunk, tiles_n, abs_in, partial, skip);
 }
 
 }  // namespace
@@ -410,7 +401,8 @@ hipError_t launch_gemm_abt(const double* A, const double* B, int m, int n, int64
   const int tiles_n = (n + abt_tile(n) - 1) / abt_tile(n);
   const int wk = 4 / (sm.w * sn.w);
   // a product of one operand with itself is symmetric, bit for bit (the same
-  // products in the same order): the tiles above the diagonal are mirrored
+  // products in the same order): the tiles above the diagonal are mirrored.  More
+  // than one tile: more than 128 rows, which are large tiles
   const bool sym = A == B && m == n && tiles_m > 1;
   const int tiles = sym ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
   nsplit = std::min(nsplit, abt_splits(m, n, K, tiles));
@@ -422,7 +414,7 @@ hipError_t launch_gemm_abt(const double* A, const double* B, int m, int n, int64
   const dim3 grid(tiles, nsplit);
 #define ACEX_ABT(RM, WM, RN, WN)                                                              \
   if (sm.r == RM && sm.w == WM && sn.r == RN && sn.w == WN)                                   \
-    abt_launch<RM, WM, RN, WN>(vec, grid, s, A, B, m, n, K, kchunk, tiles_n, sym, abs_inputs, \
+    abt_launch<RM, WM, RN, WN>(vec, grid, s, A, B, m, n, K, kchunk, tiles_n, abs_inputs,      \
                                partial, skip);
 #define ACEX_ABT_ROW(RM, WM) \
   ACEX_ABT(RM, WM, 1, 1) ACEX_ABT(RM, WM, 2, 1) ACEX_ABT(RM, WM, 4, 1)

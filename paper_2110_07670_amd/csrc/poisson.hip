@@ -2481,12 +2481,30 @@ static hipError_t zinv_t(const GridArgs& g, bool diag, const void* S, const void
     return zinv_launch<T, N, B, true>(g, diag, S, phi, W, orbs, alpha, fresh, s, S2, orbs2);
 }
 
+// The grids whose incomplete tiles take the fused pass, against the four-pass
+// form (build + apply or screened build; ms):
+//   FP64, up to 120^3: ragged 64^3 x 23 orbitals 1.23 -> 0.78, 80^3 x 75 15.3
+//     -> 14.0, 120^3 x 100 101.1 -> 96.5; screened 96^3 x 128 22.0 -> 18.5,
+//     120^3 x 128 37.6 -> 29.5.  At 128^3 its 1024 threads spill: screened
+//     x 100 35.4 -> 42.4.
+//   FP32, ragged: 40^3 x 9 0.197 -> 0.089, 128^3 x 57 23.6 -> 21.9; screened
+//     96^3 x 160 21.5 -> 20.9, 80^3 x 140 11.7 -> 12.0, 128^3 x 200 49.7 ->
+//     50.1: the W rows of a sparse tile outweigh its FP32 transforms, so that
+//     only tiles with every pair kept take it (list_ok).  Not below 40^3 and at
+//     120^3: there the two forms of the x pass fuse the Coulomb product
+//     differently, and builds that take four passes would change W in the
+//     eighth digit.
+template <typename T, int N>
+constexpr bool list_grid() {
+  return sizeof(T) == 8 ? N <= 120 : N >= 40 && N != 120;
+}
+
 template <typename T, int N, int B>
 static hipError_t zinv_list_t(const GridArgs& g, bool diag, const void* S, const void* phi,
                               double* W, const int* orbs, const int* jorbs,
                               const TileGroup* groups, int ngroups,
                               unsigned useI, unsigned useJ, unsigned fresh, double alpha, hipStream_t s) {
-  if constexpr (zinv_ok<T, N, B>()) {
+  if constexpr (zinv_ok<T, N, B>() && list_grid<T, N>()) {
     const dim3 grid(N * (N / zinv_rows<T, N>())), block(zinv_threads<T, N>());
     if (diag)
       hipLaunchKernelGGL((k_zinv_list<T, N, B, true>), grid, block, 0, s,
@@ -2582,20 +2600,15 @@ bool three_pass_ok(int n, int prec, int block) {
   }
 }
 
-// The fused pass of incomplete tiles against the four-pass form (build + apply
-// or screened build; ms):
-//   FP64, up to 120^3: ragged 64^3 x 23 orbitals 1.23 -> 0.78, 80^3 x 75 15.3
-//     -> 14.0, 120^3 x 100 101.1 -> 96.5; screened 96^3 x 128 22.0 -> 18.5,
-//     120^3 x 128 37.6 -> 29.5.  At 128^3 its 1024 threads spill: screened
-//     x 100 35.4 -> 42.4.
-//   FP32, ragged: 40^3 x 9 0.197 -> 0.089, 128^3 x 57 23.6 -> 21.9; screened
-//     96^3 x 160 21.5 -> 20.9, 80^3 x 140 11.7 -> 12.0, 128^3 x 200 49.7 ->
-//     50.1: the W rows of a sparse tile outweigh its FP32 transforms.  At
-//     120^3 and below 40^3 the two forms contract different multiply-adds,
-//     and there FP32 tiles keep the four-pass form's values.
 bool list_ok(int n, int prec, int block, bool complete) {
-  if (!three_pass_ok(n, prec, block)) return false;
-  return prec == 0 ? n <= 120 : complete && n >= 40 && n != 120;
+  if (!three_pass_ok(n, prec, block) || (prec != 0 && !complete)) return false;
+  switch (n) {
+#define X(N) \
+  case N: return prec == 0 ? list_grid<double, N>() : list_grid<float, N>();
+    ACEX_SIZES(X)
+#undef X
+    default: return false;
+  }
 }
 
 bool fused_rows_ok(int n, int prec, int block) {

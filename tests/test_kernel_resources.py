@@ -97,3 +97,10 @@ def test_slab_forward_has_no_scratch(kernels):
     assert got
     for name, (_, scratch, _) in got.items():
         assert scratch == 0, (name, scratch)
+
+
+def test_incomplete_tile_kernels_are_reached(kernels):
+    """The fused pass of incomplete tiles is compiled for the grids that take it."""
+    grids = {t: {k[2][0] for k in kernels if k[0] == "k_zinv_list" and k[1] == t} for t in "df"}
+    assert grids["d"] == {16, 24, 32, 40, 48, 64, 80, 96, 120}
+    assert grids["f"] == {40, 48, 64, 80, 96, 128}
