@@ -39,11 +39,11 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_water32_n96.md")
 KERNEL_SOURCE = os.path.join(ROOT, "paper_2110_07670_amd", "csrc", "poisson.hip")
 
 
-def tile_plan(n_orb, block, full_kind="three_pass"):
+def tile_plan(n_orb, block, full_kind="three_pass", ragged_kind="four_pass"):
     """(bi, bj, diag, npack, kind) for every tile of the unmasked schedule;
     kind: the passes the tile takes ("three_pass", "rows_fused" or
     "four_pass"; full tiles take the plan's full-tile schedule, the library's
-    ace_plan_schedule, the others four passes)."""
+    ace_plan_schedule, those of a ragged last block ragged_kind)."""
     out = []
     nb = (n_orb + block - 1) // block
     for I in range(nb):
@@ -52,17 +52,21 @@ def tile_plan(n_orb, block, full_kind="three_pass"):
             bj = min(block, n_orb - J * block)
             # two pairs of one row share a transform; a row's odd leftover is alone
             rows = [bi - a for a in range(bi)] if I == J else [bj] * bi
-            kind = full_kind if bi == block and bj == block else "four_pass"
+            kind = full_kind if bi == block and bj == block else ragged_kind
             out.append((bi, bj, I == J, sum((r + 1) // 2 for r in rows), kind))
     return out
 
 
 def plan_tiles(plan):
     kind, plane = plan.schedule()
-    return tile_plan(plan.n_orb, plan.tiling[0], kind), plane
+    # ragged tiles take three passes with the full ones in FP64 up to 120^3 and
+    # in FP32 from 40^3 on but for 120^3 (include/ace.h, ACE_SCHEDULE_AUTO)
+    three = plan.n <= 120 if plan.precision == 0 else plan.n >= 40 and plan.n != 120
+    ragged = "three_pass" if kind == "three_pass" and three else "four_pass"
+    return tile_plan(plan.n_orb, plan.tiling[0], kind, ragged), plane
 
 
-def algorithmic_bytes(stage, tiles, npts, bulk, plane=True):
+def algorithmic_bytes(stage, tiles, npts, bulk, plane=True, first_rows=0):
     """Compulsory HBM bytes of one step's launches of `stage` in this design.
 
     Per packed transform (two pairs) and grid point, c = one complex value:
@@ -73,7 +77,8 @@ def algorithmic_bytes(stage, tiles, npts, bulk, plane=True):
     row-fused tiles (the inverse y lines); w_accumulate reads c.
     Orbital traffic is counted once per tile: yz_fwd reads the tile's
     orbitals (8 B/pt each); w_accumulate reads them and reads + writes their
-    W rows (24 B/pt each).
+    W rows (24 B/pt each), but for first_rows of these that are written at
+    their first update and not read (without a mask every orbital's).
     """
     c = 2 * bulk
     tot = 0
@@ -90,6 +95,8 @@ def algorithmic_bytes(stage, tiles, npts, bulk, plane=True):
             tot += npack * 2 * c * npts
         elif stage == "w_accumulate":
             tot += (npack * c + orbs * 24) * npts
+    if stage == "w_accumulate":
+        tot -= first_rows * 8 * npts
     return tot
 
 
@@ -372,7 +379,7 @@ def run_batch(args):
             ms, cnt = prof[s]
             agg[s][0] += ms
             agg[s][1] += cnt
-            agg[s][2] += algorithmic_bytes(s, tiles, sp.n ** 3, bulk, plane)
+            agg[s][2] += algorithmic_bytes(s, tiles, sp.n ** 3, bulk, plane, p.n_orb)
     stages = {s: {"ms": round(v[0], 3), "launches": v[1],
                   "alg_GBps": v[2] / (v[0] * 1e-3) / 1e9 if v[0] else None}
               for s, v in agg.items()}
@@ -587,7 +594,7 @@ def main():
             stages[name] = {"ms_per_step": ms / args.steps, "launches_per_step": cnt // args.steps}
     for name in mem_stages:
         if name in stages:
-            ab = algorithmic_bytes(name, tiles, npts, bulk, plane)
+            ab = algorithmic_bytes(name, tiles, npts, bulk, plane, plan.n_orb)
             launch_ms = stages[name]["ms_per_step"] / stages[name]["launches_per_step"]
             gbps = ab / (stages[name]["ms_per_step"] * 1e-3) / 1e9
             stages[name]["alg_GBps"] = gbps
