@@ -605,6 +605,8 @@ __global__ __launch_bounds__(1024) void k_ns_tail(double* Y0, double* Y1, double
                                                   int it0, int iters, double* err, int* state) {
   if (state[0] != 0) return;
   const int T = (k + 15) / 16, wave = threadIdx.x >> 6;
+  int below = 0;  // errors of the iterations so far below 1e-10 (ns_done)
+  for (int q = 0; q < it0; ++q) below += err[q] < 1e-10;
   for (int it = it0; it < iters; ++it) {
     double* Y = (it & 1) ? Y1 : Y0;
     double* Yn = (it & 1) ? Y0 : Y1;
@@ -617,10 +619,8 @@ __global__ __launch_bounds__(1024) void k_ns_tail(double* Y0, double* Y1, double
     }
     __threadfence();
     __syncthreads();
-    // read past the caches, where the maxima were formed
-    int below = 0;
-    for (int q = 0; q <= it; ++q)
-      below += __hip_atomic_load(&err[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < 1e-10;
+    // read past the caches, where the maximum was formed
+    below += __hip_atomic_load(&err[it], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < 1e-10;
     if (below > 2) {
       if (threadIdx.x == 0) {
         state[0] = 1;
@@ -722,10 +722,10 @@ hipError_t launch_scdm_qr(const double* phi, const int* points, int m, int k, in
 // orbitals, 0.45 at 192 and 7 at 512, where a launched one takes 10 to 50 us.
 // Past 128 orbitals all are therefore launched (a whole localisation with 256:
 // 3.58 -> 3.76 ms where 20 iterations do, 47.1 -> 4.6 at a condition number of
-// 1e12, 12.7 -> 4.2 at 1e6; with 512 96.5 -> 12.8); from 65 on 48 of them (128
-// at 1e12 7.7 -> 6.8 ms).
+// 1e12, 12.7 -> 4.2 at 1e6; with 512 96.5 -> 12.8); from 65 on 44 of them (128
+// at 1e12 7.4 -> 6.9 ms, at 1e6 2.9 -> 2.4, where 20 do 1.647 -> 1.659).
 static int ns_launched(int k, int max_iter) {
-  return std::min(k > 128 ? max_iter : k > 64 ? 48 : 40, max_iter);
+  return std::min(k > 128 ? max_iter : k > 64 ? 44 : 40, max_iter);
 }
 
 hipError_t launch_scdm_polar(const double* phi, const int* pivots, int k, int64_t npts, double* Y,
