@@ -980,11 +980,14 @@ __device__ __forceinline__ void zinv_item(const cx<T>* __restrict__ S,
   }
   // all B rows of W are read before any is written: a store followed by the
   // next row's load would have to wait for that load (the compiler cannot
-  // tell the rows apart), one memory round trip per row.  Rows that nothing
-  // was added to before are written by a path of their own: one path with old
-  // values or zeros cost the persistent form 13 to 16 registers, and at 64^3
-  // FP32 (126 against 142) the second workgroup of a CU
-  if (fresh) {
+  // tell the rows apart), one memory round trip per row.  fresh: nothing was
+  // added to these rows before, they are written without being read.  In the
+  // persistent form up to 64^3 by a path of its own: one path with old values or
+  // zeros cost it 16 registers, 126 against 142, and with them the second
+  // workgroup of a CU (64^3 FP32); on larger planes, one workgroup per CU in
+  // either case, the one path is 0.2% faster
+  constexpr bool OWN = LOOP && N <= 64;
+  if (OWN && fresh) {
     if (act) {
 #pragma unroll
       for (int b = 0; b < B; ++b)
@@ -995,8 +998,12 @@ __device__ __forceinline__ void zinv_item(const cx<T>* __restrict__ S,
   }
   double wold[B];
 #pragma unroll
-  for (int b = 0; b < B; ++b)
-    wold[b] = __builtin_nontemporal_load(&W[(int64_t)orbs[(DIAG ? 0 : B) + b] * npts + r]);
+  for (int b = 0; b < B; ++b) wold[b] = 0.0;
+  if (OWN || !fresh) {
+#pragma unroll
+    for (int b = 0; b < B; ++b)
+      wold[b] = __builtin_nontemporal_load(&W[(int64_t)orbs[(DIAG ? 0 : B) + b] * npts + r]);
+  }
   if (act) {
 #pragma unroll
     for (int b = 0; b < B; ++b)
