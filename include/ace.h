@@ -137,7 +137,10 @@ int ace_apply_noalloc(const ace_plan *plan, void *stream, const double *xi, cons
  *   ex      device double output.
  *   pair_e  NULL, or device [n_orb][n_orb] double: entry (i, j), i <= j, gets
  *           that pair's share -alpha (2 - delta_ij) (ij|ji); other entries are
- *           left untouched.  Two pairs share a transform in either case. */
+ *           left untouched.  FP32: one pair per transform.  FP64: two pairs of
+ *           a row share one where that saves time; they are brought level and
+ *           told apart, so that each keeps its own digits, and a pair that is
+ *           not finite, or zero, does not show in the other. */
 int exx_energy(const ace_plan *plan, void *stream, void *ws, size_t ws_bytes, const double *phi,
                const uint8_t *pair_mask, double *ex, double *pair_e);
 

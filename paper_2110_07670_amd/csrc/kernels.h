@@ -191,7 +191,8 @@ hipError_t launch_gemm_abt(const double* A, const double* B, int m, int n, int64
                            bool abs_inputs, const int* skip_if_nonzero, hipStream_t s);
 int gemm_abt_splits(int m, int n, int64_t K);
 // Out[m][r] = scale * sum_k A[m][k] B[k][r]; A (m x k, k <= 512) row-major small,
-// B (k x R) row-major.  tri: A is lower triangular (its upper part is not read).
+// B (k x R) row-major.  tri: A is lower triangular, with zeros stored above the
+// diagonal (the 16 x 16 blocks on it are multiplied whole, those above are not read).
 hipError_t launch_gemm_ab(const double* A, const double* B, int m, int k, int64_t R,
                           double scale, double* Out, bool tri, const int* skip_if_nonzero,
                           hipStream_t s);
