@@ -44,9 +44,11 @@ def stage_of(name: str) -> str:
         p = name.split("k_batch_pass<")[1].split(">")[0].split(",")[1].strip()
         return {"0": "yz_fwd", "1": "x_poisson", "2": "w_accumulate"}.get(p, "other")
     if "k_lines" in name:
-        # third template argument MODE: 0 Poisson (x), 1 energy, 2 y forward, 3 y inverse
+        # third template argument MODE: 0 Poisson (x), 1 energy (4 with streaming
+        # loads), 2 y forward, 3 y inverse
         mode = name.split("k_lines<")[1].split(">")[0].split(",")[2].strip()
-        return {"0": "x_poisson", "1": "x_energy", "2": "yz_fwd", "3": "yz_inv"}.get(mode, "lines")
+        return {"0": "x_poisson", "1": "x_energy", "2": "yz_fwd", "3": "yz_inv",
+                "4": "x_energy"}.get(mode, "lines")
     for key, st in STAGE_OF:
         if key in name:
             return st

@@ -32,3 +32,10 @@ def test_first_rows_are_not_read():
     all_read = bench.algorithmic_bytes("w_accumulate", tiles, npts, 8)
     assert all_read - bench.algorithmic_bytes("w_accumulate", tiles, npts, 8, True, 128) \
         == 128 * 8 * npts
+
+
+@pytest.mark.parametrize("mode,stage", [(0, "x_poisson"), (1, "x_energy"), (4, "x_energy"),
+                                        (2, "yz_fwd"), (3, "yz_inv")])
+def test_line_kernels_have_a_stage(mode, stage):
+    from paper_2110_07670_amd import profiling
+    assert profiling.stage_of("void acex::k_lines<double, 96, %d, 16>(float)" % mode) == stage
