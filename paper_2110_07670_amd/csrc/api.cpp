@@ -522,8 +522,8 @@ bool share_pair_energies(const ace_plan* p, const uint8_t* mask) {
   if (p->prec != ACE_FP64) return false;
   int64_t saved = 0;
   for (int i = 0; i < p->n_orb; ++i) {
-    int kept = 0;
-    for (int j = i; j < p->n_orb; ++j) kept += mask_on(mask, p->n_orb, i, j);
+    int kept = mask ? 0 : p->n_orb - i;
+    for (int j = i; mask && j < p->n_orb; ++j) kept += mask_on(mask, p->n_orb, i, j);
     saved += kept / 2;
   }
   const double k = p->n_orb, npts = (double)p->npts;
